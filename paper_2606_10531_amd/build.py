@@ -10,7 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "liblcvq.so")
-SOURCES = ["lcvq_api.hip", "lcvq_prep.hip", "lcvq_gemm.hip", "lcvq_f32.hip", "lcvq_adam.hip", "lcvq_packed.hip", "lcvq_encode.hip"]
+SOURCES = ["lcvq_api.hip", "lcvq_prep.hip", "lcvq_gemm.hip", "lcvq_split.hip", "lcvq_f32.hip", "lcvq_adam.hip", "lcvq_packed.hip", "lcvq_encode.hip"]
 ARCH = "gfx950"
 # Packed fp32 instructions are kept out of every kernel; the host pass warns
 # that it does not know the feature, which is harmless.
@@ -22,7 +22,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # The products' epilogues issue matrix-core instructions through the compiler's
 # builtins, accumulating in vector registers (the accumulator registers hold the
 # main loop's results): select the vector-register form for them.
-PER_FILE_FLAGS = {"lcvq_gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=true"]}
+PER_FILE_FLAGS = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form=true"] for s in ("lcvq_gemm.hip", "lcvq_split.hip")}
 
 
 def hipcc() -> str:

@@ -28,107 +28,14 @@
 // after the loop (mfma_drain).  All other operands come from loads, which the
 // compiler's waits cover.  The input gradient's epilogue products (the A-map
 // and the map gradient) use the compiler's builtin, whose hazards it handles.
+#include "lcvq_mfma.hpp"
 #include "lcvq_prep.hpp"
 
 namespace lcvq {
 
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-
-constexpr int kTile = 256;   // block tile (M and N)
-constexpr int kKStep = 64;   // K per main-loop step
-
-// s_waitcnt with every counter at zero.
-#define LCVQ_WAIT_ALL() __builtin_amdgcn_s_waitcnt(0)
-// s_waitcnt vmcnt(N) lgkmcnt(0) (gfx9 encoding; expcnt left at its maximum).
-#define LCVQ_WAIT_VM_LGKM0(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4))
-// s_waitcnt vmcnt(N) only (lgkmcnt and expcnt left at their maximum).
-#define LCVQ_WAIT_VM(N) __builtin_amdgcn_s_waitcnt(((N) & 15) | (((N) >> 4) << 14) | (7 << 4) | (15 << 8))
-// s_waitcnt lgkmcnt(0) only.
-#define LCVQ_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4))
-// Workgroup barrier without the release fence of __syncthreads() (which would
-// drain the prefetch loads); the asm statements keep the compiler from moving
-// memory operations across it.  LDS visibility is ensured by the waits above.
-#define LCVQ_BARRIER()                   \
-  do {                                   \
-    asm volatile("" ::: "memory");       \
-    __builtin_amdgcn_s_barrier();        \
-    asm volatile("" ::: "memory");       \
-  } while (0)
-
-// Blocks are dispatched round-robin over the eight XCDs.  Give each XCD a
-// contiguous run of tile ids, and walk tiles in bands of eight M-tiles, so the
-// blocks sharing an XCD's L2 share operand tiles (with 256 tiles: 8 M-tiles x
-// 4 token tiles per XCD, the fewest operand bytes per L2 for these products).
-__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int nblocks = (int)gridDim.x;
-  int id = (int)blockIdx.x;
-  if (nblocks % 8 == 0) id = (id % 8) * (nblocks / 8) + id / 8;
-  constexpr int GM = 8;
-  const int band = id / (GM * tiles_n);
-  const int first = band * GM;
-  const int gm = min(tiles_m - first, GM);
-  const int in = id - band * GM * tiles_n;
-  tm = first + in % gm;
-  tn = in / gm;
-}
-
-// acc = A * B + acc, operands loaded (no VALU producer): issued in program order.
-__device__ __forceinline__ void mfma16(floatx4 &acc, const bf16x8 &a, const bf16x8 &b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-// The same with A produced by VALU instructions: the leading s_nop covers the
-// VALU-write to matrix-core-read wait states.
-__device__ __forceinline__ void mfma16_valu_a(floatx4 &acc, const bf16x8 &a, const bf16x8 &b) {
-  asm volatile("s_nop 2\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-// Wait states between the zeroing of the accumulators (vector writes) and the
-// first matrix-core read of them, R x C accumulators.  Each statement passes
-// four accumulators through itself, so every zeroing write precedes the whole
-// chain and every MFMA follows it: at least R C / 4 statements and a final
-// s_nop 4 lie between a write and a read.
-template <int R, int C>
-__device__ __forceinline__ void acc_fence(floatx4 (&acc)[R][C]) {
-  static_assert(C % 4 == 0, "four accumulators per statement");
-#pragma unroll
-  for (int i = 0; i < R; ++i)
-#pragma unroll
-    for (int j = 0; j < C; j += 4) {
-      if (i + 1 < R || j + 4 < C)
-        asm volatile("s_nop 0" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]), "+a"(acc[i][j + 2]), "+a"(acc[i][j + 3]));
-      else
-        asm volatile("s_nop 4" : "+a"(acc[i][j]), "+a"(acc[i][j + 1]), "+a"(acc[i][j + 2]), "+a"(acc[i][j + 3]));
-    }
-}
-// Wait states between the last matrix-core write of an accumulator and the
-// epilogue's vector reads of it.  The statement is a scheduling boundary with
-// a memory clobber; the reads are copies the compiler places at their uses,
-// which all lie in the epilogue after it.
-__device__ __forceinline__ void mfma_drain() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
-
-// The codes conversion as ordered inline assembly: it stays where it is written
-// (between two MFMAs of the previous operand), so the two MFMAs that follow it
-// supply the wait states its consumer needs.
-__device__ __forceinline__ bf16x8 nibbles_to_bf16x8_ordered(uint32_t w) {
-  uint32_t p0, p1, p2, p3;
-  asm volatile("v_cvt_scalef32_pk_bf16_fp4 %0, %1, 2.0" : "=v"(p0) : "v"(w));
-  asm volatile("v_cvt_scalef32_pk_bf16_fp4 %0, %1, 2.0 op_sel:[1,0,0]" : "=v"(p1) : "v"(w));
-  asm volatile("v_cvt_scalef32_pk_bf16_fp4 %0, %1, 2.0 op_sel:[0,1,0]" : "=v"(p2) : "v"(w));
-  asm volatile("v_cvt_scalef32_pk_bf16_fp4 %0, %1, 2.0 op_sel:[1,1,0]" : "=v"(p3) : "v"(w));
-  return __builtin_bit_cast(bf16x8, u32x4{p0, p1, p2, p3});
-}
-
-__device__ __forceinline__ float as_f(uint32_t u) { return __uint_as_float(u); }
-// Copy a (uniform) value into a vector register.
-__device__ __forceinline__ float to_vgpr(float x) {
-  float v;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(v) : "s"(x));
-  return v;
-}
-__device__ __forceinline__ uint32_t as_u(float f) { return __float_as_uint(f); }
-
 // ============================================================================
-// Products with codes as the A operand (forward, input gradient).
+// Products with codes as the A operand (forward, input gradient), wide tiles
+// (lcvq_split.hip has the small ones and the rule between them).
 // Each wave owns 256 weight-side rows x 64 tokens (where those sit in the
 // block tile is set at the top of the kernel) and streams both operands
 // straight into registers, with no LDS stage: the codes of its eight 32-row
@@ -780,6 +687,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_dw(const uint16_t *__restrict__
 hipError_t launch_fwd_bf16(const uint32_t *frag, const uint16_t *Xp, int64_t ldp, const float *s,
                            uint16_t *Y, int64_t N, int64_t m, int64_t n, hipStream_t st) {
   (void)n;
+  if (const int slabs = fwd_slabs(N, m)) return launch_fwd_split(slabs, frag, Xp, ldp, s, Y, N, m, st);
   const int tiles_m = (int)ceil_div(m, 2 * kTile), tiles_n = (int)ceil_div(N, kTile / 2);  // 512 x 128 tiles
   const int KB = (int)(ldp / kKStep);  // even: ldp is a multiple of 128
   const int64_t Np = round_up(N, kTile);  // row stride of the partial sums of s
@@ -791,6 +699,7 @@ hipError_t launch_fwd_bf16(const uint32_t *frag, const uint16_t *Xp, int64_t ldp
 hipError_t launch_dx_bf16(const uint32_t *frag, const uint16_t *dY, const float *rsp, const float *A, const float *b,
                           int d, uint16_t *dX, const uint16_t *X, float *mapp, int64_t N, int64_t m, int64_t n,
                           hipStream_t st) {
+  if (const int slabs = dx_slabs(N, n)) return launch_dx_split(slabs, frag, dY, rsp, A, b, d, dX, X, mapp, N, m, n, st);
   const int parts = rowsum_parts(m);
   const int64_t Nt = bwd_tokens(N);  // row stride of the partial row sums
   const int tiles_m = (int)ceil_div(n, kTile), tiles_n = (int)ceil_div(N, kTile);
@@ -805,7 +714,10 @@ hipError_t launch_dx_bf16(const uint32_t *frag, const uint16_t *dY, const float 
   return hipGetLastError();
 }
 
-int map_rows(int64_t N, int64_t n) { return (int)(ceil_div(n, kTile) * ceil_div(N, kTile)); }
+int map_rows(int64_t N, int64_t n) {
+  const int slabs = dx_slabs(N, n);
+  return (int)(slabs ? ceil_div(n, 32 * slabs) * ceil_div(N, 64) : ceil_div(n, kTile) * ceil_div(N, kTile));
+}
 
 // Entry blockIdx.x of dA (< D D) or db: the sum of its `rows` per-block
 // partial sums in a fixed order (thread i: rows i, i + 256, ...; then a

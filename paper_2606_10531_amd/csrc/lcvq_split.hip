@@ -1,0 +1,401 @@
+// The codes products (forward, input gradient) for shapes whose wide tiles
+// (k_gemm_codes, lcvq_gemm.hip) would leave compute units idle: few tokens, few
+// out- or in-features, or a last round of tiles that is nearly empty.
+//
+// Block tile 32 MI weight-side rows x 64 tokens.  The block's four waves split
+// K (wave w takes the 64-wide steps w, w + 4, ..., so together they read 256
+// consecutive K of every activation row), each with an accumulator of the whole
+// tile, and add their sums through LDS in a fixed order at the end.  A block does
+// an eighth (MI = 4) or a sixteenth (MI = 2) of a wide tile's work with the same
+// matrix-core instructions per converted codes operand, and two blocks share a
+// compute unit, so one's epilogue runs under the other's products.  What bounds
+// it: with the chip full, operand traffic (the waves share nothing: 64 tokens x 64
+// K of activations and MI KiB of codes per step and wave); with one block per
+// compute unit, that traffic's 64 bytes per clock into the unit and its latency.
+// Operand layouts, the codes conversion and the epilogues are those of
+// k_gemm_codes.
+#include "lcvq_mfma.hpp"
+#include "lcvq_prep.hpp"
+
+namespace lcvq {
+
+constexpr int kW = 4;  // waves of a block, each on its own part of K
+
+// kMode 0: forward (B = X' fragments), 1: input gradient (B = dY, row length ldB)
+template <int kMode, int D, int MI>
+__global__ __launch_bounds__(256, 2) void k_codes_split(
+    const uint32_t *__restrict__ frag, int KB, const uint16_t *__restrict__ Bsrc, int64_t ldB, int tiles_m,
+    int tiles_n, const float *__restrict__ vecT, int vparts, int64_t vstride, const float *__restrict__ A,
+    const float *__restrict__ bvec, uint16_t *__restrict__ out, int64_t ldo, int64_t Mvalid, int64_t Tvalid,
+    const uint16_t *__restrict__ X, float *__restrict__ mapp) {
+  constexpr int P = 2 * MI;  // 16-row blocks of the tile
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  tile_of_block(tiles_m, tiles_n, tm, tn);
+  const int64_t tw = (int64_t)tn * 64;
+
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(frag + (size_t)(tm * MI) * KB * 256, (int64_t)MI * KB * 1024);
+  const __amdgpu_buffer_rsrc_t rsB =
+      kMode == 0 ? make_rsrc(Bsrc + (tw >> 5) * (int64_t)KB * 2048, (int64_t)2 * KB * 4096)
+                 : make_rsrc(Bsrc + tw * ldB, (Tvalid - tw < 64 ? Tvalid - tw : 64) * ldB * 2);
+  floatx4 acc[P][4];  // [row block 2 mi + rb][16-token block tb]
+#pragma unroll
+  for (int i = 0; i < P; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  acc_fence(acc);
+
+  // Codes: two register buffers of one step each (steps past KB load nothing and
+  // read as zero).  The conversion of the next operand is placed between the
+  // MFMAs of the current one, as in k_gemm_codes.
+  u32x4 ca[2][MI];
+  auto load_a = [&](int buf, int kb) {
+    const bool live = kb < KB;
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+      ca[buf][mi] = __builtin_amdgcn_raw_buffer_load_b128(rsA, live ? lane * 16 : (int)kOffNone,
+                                                          live ? (mi * KB + kb) * 1024 : 0, 0);
+  };
+  auto conv = [&](int buf, int s2) {  // operand s2 = P kk2 + 2 mi + rb of a step
+    const int kk2 = s2 / P, p = s2 % P;
+    return nibbles_to_bf16x8_ordered(ca[buf][p >> 1][2 * (p & 1) + kk2]);
+  };
+  // the MFMAs of half-step kk2: b[tb] the four token blocks' operands
+  auto half = [&](int buf, int kk2, bf16x8 &an, const u32x4 (&b)[4]) {
+    if (kk2 == 0) an = conv(buf, 0);
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      const int s2 = P * kk2 + p;
+      const bf16x8 a = an;
+      if (s2 == 0) mfma16_valu_a(acc[p][0], a, __builtin_bit_cast(bf16x8, b[0]));
+      else mfma16(acc[p][0], a, __builtin_bit_cast(bf16x8, b[0]));
+      mfma16(acc[p][1], a, __builtin_bit_cast(bf16x8, b[1]));
+      if (s2 + 1 < 2 * P) an = conv(buf, s2 + 1);
+      mfma16(acc[p][2], a, __builtin_bit_cast(bf16x8, b[2]));
+      mfma16(acc[p][3], a, __builtin_bit_cast(bf16x8, b[3]));
+    }
+  };
+  __shared__ __attribute__((aligned(1024))) char lds[kW * 16384];  // dY stages (kMode 1), then the waves' sums
+
+  if constexpr (kMode == 0) {
+    // X' fragments: whole 1 KiB per load, straight into registers, two steps ahead
+    u32x4 cb[2][2][4];  // [buffer][half-step][token block]
+    auto load = [&](int buf, int kb) {
+      load_a(buf, kb);
+#pragma unroll
+      for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+        for (int kk2 = 0; kk2 < 2; ++kk2)
+          cb[buf][kk2][tb] = __builtin_amdgcn_raw_buffer_load_b128(
+              rsB, kb < KB ? (int)(((((tb >> 1) * KB + kb) * 4) + 2 * (tb & 1) + kk2) * 1024 + lane * 16) : (int)kOffNone,
+              0, 0);
+    };
+    load(0, wave);
+    __builtin_amdgcn_sched_barrier(0);
+    load(1, wave + kW);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int kb = wave; kb < KB; kb += 2 * kW) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        bf16x8 an;
+        half(u, 0, an, cb[u][0]);
+        half(u, 1, an, cb[u][1]);
+        __builtin_amdgcn_sched_barrier(0);
+        load(u, kb + (2 + u) * kW);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else {
+    // dY rows.  Lanes that follow each other must read memory that follows each
+    // other: with the operand's own mapping (neighbouring lanes = tokens, a row
+    // apart) a 1 KiB load takes the address path 64 cycles instead of 16
+    // (measured 8.5 against 23 TB/s from the L2).  So lane L loads chunk L % 8 (16
+    // bytes) of row 8 r + L / 8, whole 128-byte lines, and the wave's own LDS
+    // stage turns that into operands: row t's chunk k at 128 t + 16 (k ^ (t % 8)),
+    // which keeps both the writes and the reads free of bank conflicts.  Only the
+    // wave itself uses its stages, so no barrier is needed.
+    constexpr int kG = MI == 4 ? 1 : 2;  // steps of dY in registers (MI = 4: two would leave no room for a second block)
+    u32x4 g[kG][8], b0[4], b1[4];
+    char *stage = lds + wave * 16384;
+    const int lrow = lane >> 3, lch = lane & 7;
+    const uint32_t goff = (uint32_t)((lrow * ldB + 8 * lch) * 2);
+    const uint32_t woff = (uint32_t)(lrow * 128 + ((lch ^ lrow) << 4));
+    const uint32_t roff = (uint32_t)(c16 * 128 + ((q ^ (c16 & 7)) << 4));
+    const int kb_lim = (int)ldB - 8 - 8 * lch;  // the lane's chunk exists at step kb iff 64 kb <= kb_lim
+    const uint32_t gstep = (uint32_t)(16 * ldB);  // eight rows
+    auto load_g = [&](u32x4 (&v)[8], int kb) {
+      const uint32_t off = kb < KB && kb * 64 <= kb_lim ? goff + (uint32_t)kb * 128u : kOffNone;
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        v[r] = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(off == kOffNone ? kOffNone : off + r * gstep), 0, 0);
+    };
+    auto put = [&](const u32x4 (&v)[8], int st) {
+#pragma unroll
+      for (int r = 0; r < 8; ++r) *reinterpret_cast<u32x4 *>(stage + st * 8192 + r * 1024 + woff) = v[r];
+    };
+    auto get = [&](u32x4 (&b)[4], int st, int kk2) {
+#pragma unroll
+      for (int tb = 0; tb < 4; ++tb)
+        b[tb] = *reinterpret_cast<const u32x4 *>(stage + st * 8192 + tb * 2048 + (roff ^ (kk2 << 6)));
+    };
+    load_a(0, wave);
+    load_g(g[0], wave);
+    __builtin_amdgcn_sched_barrier(0);
+    load_a(1, wave + kW);
+    if constexpr (kG == 2) load_g(g[1], wave + kW);
+    __builtin_amdgcn_sched_barrier(0);
+    put(g[0], 0);
+    load_g(g[0], wave + kG * kW);
+    get(b0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int kb = wave; kb < KB; kb += 2 * kW) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        bf16x8 an;
+        const int k = kb + kW * u;
+        get(b1, u, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        half(u, 0, an, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        put(g[(u + 1) % kG], u ^ 1);
+        load_g(g[(u + 1) % kG], k + (1 + kG) * kW);
+        __builtin_amdgcn_sched_barrier(0);
+        half(u, 1, an, b1);
+        __builtin_amdgcn_sched_barrier(0);
+        get(b0, u ^ 1, 0);
+        load_a(u, k + 2 * kW);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    __syncthreads();  // the stages become the waves' sums
+  }
+  mfma_drain();
+
+  // ---------------------------------------------------------------- epilogue
+  // After the sum, wave w holds 16-token block tb = w of the tile: lane L the 8
+  // consecutive weight-side rows c .. c + 7 (c = 32 (tm MI + mi) + 8 (L / 16)) of
+  // token t = tw + 16 w + L % 16, for each slab mi.
+  const int tl = 16 * wave + c16;
+  const int64_t cb0 = (int64_t)tm * MI * 32 + 8 * q;
+  const __amdgpu_buffer_rsrc_t ro = make_rsrc(out + tw * ldo, out == nullptr ? 0 : (Tvalid - tw) * ldo * 2);
+  // per-token term: the token's four lanes split its partial rows (as in k_gemm_codes)
+  constexpr int kMaxParts = kMaxActChunks;
+  static_assert(kMaxParts % 4 == 0, "whole parts per lane");
+  const __amdgpu_buffer_rsrc_t rv = make_rsrc(vecT + tw, ((int64_t)(vparts - 1) * vstride + Tvalid - tw) * 4);
+  float vp[kMaxParts / 4];
+#pragma unroll
+  for (int i = 0; i < kMaxParts / 4; ++i) {
+    const int p = 4 * i + q;
+    vp[i] = p < vparts ? __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rv, (int)((p * vstride + tl) * 4), 0, 0))
+                       : 0.0f;
+  }
+  const bool want_map = kMode == 1 && mapp != nullptr;
+  u32x4 xv[kMode == 1 ? MI : 1];  // X[t, c .. c + 7] per slab
+  if constexpr (kMode == 1) {
+    const __amdgpu_buffer_rsrc_t rx = make_rsrc(X + tw * Mvalid, want_map ? (Tvalid - tw) * Mvalid * 2 : 0);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int64_t c = cb0 + i * 32;
+      xv[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, c < Mvalid ? (uint32_t)(tl * Mvalid + c) * 2u : kOffNone, 0, 0);
+    }
+  }
+  float vt = vp[0];
+#pragma unroll
+  for (int i = 1; i < kMaxParts / 4; ++i) vt += vp[i];
+  vt += __shfl_xor(vt, 16, 64);
+  vt += __shfl_xor(vt, 32, 64);
+
+  // constants of the A^T map and the map-gradient sums (see k_gemm_codes)
+  bf16x8 amh[2], aml[2];
+  float bsel[2][4], gb[D];
+  floatx4 dah = floatx4{0.0f, 0.0f, 0.0f, 0.0f}, dal = dah;
+  __shared__ __attribute__((aligned(1024))) char pst[kMode == 1 ? kW * 3072 : 16];
+  const int tq = c16 & 3, te = c16 >> 2;
+  const int toff = 16 * (16 * (2 * (tq >> 1) + (q >> 1)) + 8 * (q & 1) + te) + 8 * (tq & 1);
+  auto tr8 = [&](const char *base) {
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(base + toff));
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4 *)(base + toff + 64));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  if constexpr (kMode == 1) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) gb[j] = 0.0f;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) {
+      const int cp = slab_row(16 * mb + c16);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int c = 8 * q + i;
+        const float v = cp / D == c / D ? A[(cp % D) * D + (c % D)] : 0.0f;
+        const __bf16 h = (__bf16)v;
+        amh[mb][i] = h;
+        aml[mb][i] = (__bf16)(v - (float)h);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) bsel[mb][e] = to_vgpr(bvec[(4 * mb + e) % D]);
+    }
+  }
+
+  // The four waves' sums through LDS, two slabs (four row blocks) at a time:
+  // every wave stores its four token blocks, then reads the four partial sums of
+  // its own and adds them in wave order.
+  floatx4 (*red)[4][4][64] = reinterpret_cast<floatx4 (*)[4][4][64]>(lds);  // [source wave][tb][row block][lane]
+#pragma unroll
+  for (int ph = 0; ph < MI / 2; ++ph) {
+    if (ph > 0) __syncthreads();
+#pragma unroll
+    for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        floatx4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x;
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[4 * ph + k][tb][e]));
+          r[e] = x;
+        }
+        red[wave][tb][k][lane] = r;
+      }
+    __syncthreads();
+    float pv[2][8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      floatx4 v = red[0][wave][k][lane];
+#pragma unroll
+      for (int w = 1; w < kW; ++w) v += red[w][wave][k][lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pv[k >> 1][4 * (k & 1) + e] = v[e];
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const u32x4 xp = xv[kMode == 1 ? 2 * ph + h : 0];
+      const int64_t c = cb0 + (2 * ph + h) * 32;
+      const uint32_t off = c < Mvalid ? (uint32_t)(tl * ldo + c) * 2u : kOffNone;
+      u32x4 w;
+      if constexpr (kMode == 0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(pv[h][2 * e] + vt, pv[h][2 * e + 1] + vt);
+      } else {
+        u32x4 ph_, pl_;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ph_[e] = pack_bf16x2(pv[h][2 * e], pv[h][2 * e + 1]);
+          pl_[e] = pack_bf16x2(pv[h][2 * e] - bf16_lo(ph_[e]), pv[h][2 * e + 1] - bf16_hi(ph_[e]));
+        }
+        const bf16x8 bh = __builtin_bit_cast(bf16x8, ph_), bl = __builtin_bit_cast(bf16x8, pl_);
+        float y[8];
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+          floatx4 cacc;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) cacc[e] = vt * bsel[mb][e];
+          cacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(amh[mb], bh, cacc, 0, 0, 0);
+          cacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aml[mb], bh, cacc, 0, 0, 0);
+          cacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(amh[mb], bl, cacc, 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[4 * mb + e] = cacc[e];
+        }
+        if (want_map) {
+          char *pp = pst + wave * 3072;  // this wave's X, P high, P low rows of the pair
+          *reinterpret_cast<u32x4 *>(pp + lane * 16) = xp;
+          *reinterpret_cast<u32x4 *>(pp + 1024 + lane * 16) = ph_;
+          *reinterpret_cast<u32x4 *>(pp + 2048 + lane * 16) = pl_;
+          const bf16x8 xa = tr8(pp), pbh = tr8(pp + 1024), pbl = tr8(pp + 2048);
+          dah = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, pbh, dah, 0, 0, 0);
+          dal = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa, pbl, dal, 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            gb[e % D] = fmaf((e & 1) ? bf16_hi(xp[e >> 1]) : bf16_lo(xp[e >> 1]), vt, gb[e % D]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(y[2 * e], y[2 * e + 1]);
+      }
+      __builtin_amdgcn_raw_buffer_store_b128(w, ro, off, 0, 0);
+    }
+  }
+  if (want_map) {
+    constexpr int kSlots = 16 / D;
+    __shared__ float mred[kW][kSlots * D * D + D];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int mrow = 4 * q + e;
+      if (mrow / D == c16 / D) mred[wave][(mrow / D) * D * D + (mrow % D) * D + c16 % D] = dah[e] + dal[e];
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) gb[j] += __shfl_xor(gb[j], o, 64);
+    if (lane == 0) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) mred[wave][kSlots * D * D + j] = gb[j];
+    }
+    __syncthreads();
+    if (tid < D * D + D) {
+      float v = 0.0f;
+#pragma unroll
+      for (int w = 0; w < kW; ++w) {
+        if (tid < D * D) {
+#pragma unroll
+          for (int sl = 0; sl < kSlots; ++sl) v += mred[w][sl * D * D + tid];
+        } else {
+          v += mred[w][kSlots * D * D + tid - D * D];
+        }
+      }
+      mapp[(int64_t)tid * gridDim.x + blockIdx.x] = v;
+    }
+  }
+}
+
+// ---- the choice of tiles -----------------------------------------------------
+// Rounds of tiles over the 256 compute units times what a tile takes per 64-wide
+// step, measured with the chip full (ns; forward 512 x 128 wide tile, then 128 and
+// 64 rows x 64 tokens; input gradient 256 x 256 wide tile, then the same).  A full
+// wide tile costs less per output (forward 7 %, input gradient a third), so the
+// small tiles win where the wide ones leave a round partly empty: at 256 tokens and
+// 4096 x 4096, 16 wide tiles take 80 (forward) and 90 us (input gradient), 256 of
+// the smallest 12 and 17; at 1000 tokens and 11008 x 4096 the input gradient 217
+// against 82; the forward of 4096 x 11008 at 2048 tokens 213 against 128.  At 4096^3
+// every tile of one wide round is busy and stays ahead (98 against 101, 108 against
+// 129).
+int codes_split_slabs(int64_t rows, int64_t tokens, bool dx) {
+  constexpr int64_t kNs[2][3] = {{1400, 187, 117}, {1500, 240, 155}};
+  const int64_t *ns = kNs[dx ? 1 : 0];
+  auto rounds = [](int64_t tiles) { return ceil_div(tiles, 256); };
+  const int64_t wide = dx ? ceil_div(rows, 256) * ceil_div(tokens, 256) : ceil_div(rows, 512) * ceil_div(tokens, 128);
+  const int64_t tt = ceil_div(tokens, 64);
+  const int64_t c0 = ns[0] * rounds(wide), c4 = ns[1] * rounds(ceil_div(rows, 128) * tt),
+                c2 = ns[2] * rounds(ceil_div(rows, 64) * tt);
+  if (c0 <= c4 && c0 <= c2) return 0;
+  return c2 < c4 ? 2 : 4;
+}
+
+// ---- launchers -----------------------------------------------------------------
+template <int kMode, int D, int MI>
+static hipError_t split_launch(const uint32_t *frag, int KB, const uint16_t *B, int64_t ldB, const float *vec, int parts,
+                               int64_t vstride, const float *A, const float *b, uint16_t *out, int64_t rows, int64_t N,
+                               const uint16_t *X, float *mapp, hipStream_t st) {
+  const int tiles_m = (int)ceil_div(rows, 32 * MI), tiles_n = (int)ceil_div(N, 64);
+  k_codes_split<kMode, D, MI><<<tiles_m * tiles_n, 256, 0, st>>>(frag, KB, B, ldB, tiles_m, tiles_n, vec, parts, vstride,
+                                                                 A, b, out, rows, rows, N, X, mapp);
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd_split(int slabs, const uint32_t *frag, const uint16_t *Xp, int64_t ldp, const float *s, uint16_t *Y,
+                            int64_t N, int64_t m, hipStream_t st) {
+  const int KB = (int)(ldp / kKStep), parts = act_chunks(ldp);
+  const int64_t Np = round_up(N, kTile);  // row stride of the partial sums of s
+  auto go = slabs == 4 ? split_launch<0, 8, 4> : split_launch<0, 8, 2>;
+  return go(frag, KB, Xp, 0, s, parts, Np, nullptr, nullptr, Y, m, N, nullptr, nullptr, st);
+}
+
+hipError_t launch_dx_split(int slabs, const uint32_t *frag, const uint16_t *dY, const float *rsp, const float *A,
+                           const float *b, int d, uint16_t *dX, const uint16_t *X, float *mapp, int64_t N, int64_t m,
+                           int64_t n, hipStream_t st) {
+  const int KB = (int)(round_up(m, 128) / kKStep);
+  auto go = d == 8 ? (slabs == 4 ? split_launch<1, 8, 4> : split_launch<1, 8, 2>)
+                   : (slabs == 4 ? split_launch<1, 4, 4> : split_launch<1, 4, 2>);
+  return go(frag, KB, dY, m, rsp, rowsum_parts(m), bwd_tokens(N), A, b, dX, n, N, X, mapp, st);
+}
+
+}  // namespace lcvq
