@@ -268,9 +268,8 @@ size_t lcvq_packed_scratch_bytes(void);
  *   dX, dZ, dA, db  each may be NULL to skip it (dA and db are produced
  *              together: both NULL or both non-NULL)
  *   dz_dtype   element type of dZ: LCVQ_F32, or LCVQ_BF16 when dtype is bf16
- * bf16: dA/db are per-block partial sums added in a fixed order, so repeated
- * calls give the same bits.  fp32: they are summed with floating-point
- * atomics, so their last bits may vary from run to run.
+ * dA/db are per-block partial sums added in a fixed order, so repeated calls
+ * give the same bits.
  */
 lcvq_status_t lcvq_linear_bwd(int64_t N, int64_t m, int64_t n, int32_t d, int32_t dtype,
                               const void *Z, const float *A, const float *b,
@@ -407,9 +406,9 @@ typedef enum {
                            and X' = X blockdiag(A), s = X b~ */
   LCVQ_K_FWD = 1,       /* Y = X' codes^T + s 1^T */
   LCVQ_K_BWD_PREP = 2,  /* backward prepass: codes in the input-gradient operand layout, X' and dY
-                           in the weight-gradient operand layout (fp32: row sums of dY) */
+                           in the weight-gradient operand layout (bf16 only) */
   LCVQ_K_DX = 3,        /* dX (with dA, db in bf16 mode) */
-  LCVQ_K_DW = 4,        /* dZ = mask * (dY^T X') (with dA, db in fp32 mode) */
+  LCVQ_K_DW = 4,        /* dZ = mask * (dY^T X') (with dA, db partial sums in fp32 mode) */
   LCVQ_K_PACK = 5,      /* lcvq_pack2bit */
   LCVQ_K_DEQUANT = 6,   /* lcvq_dequant */
   LCVQ_K_FILL = 7,      /* zero fills of degenerate shapes */
@@ -417,7 +416,7 @@ typedef enum {
   LCVQ_K_PACKED_PREP = 9,  /* lcvq_linear_fwd_packed: X' and s of up to 16 tokens */
   LCVQ_K_PACKED = 10,      /* lcvq_linear_fwd_packed: Y from the packed codes */
   LCVQ_K_ENCODE = 11,      /* lcvq_encode */
-  LCVQ_K_MAP_SUM = 12,     /* bf16 backward: dA, db, summed over the input-gradient product's blocks */
+  LCVQ_K_MAP_SUM = 12,     /* backward: dA, db, summed over the blocks of the product that forms them */
   LCVQ_K_COUNT = 13
 } lcvq_kernel_t;
 lcvq_status_t lcvq_timer_enable(uint32_t mask);

@@ -98,7 +98,8 @@ BwdLayout bwd_layout(int64_t N, int64_t m, int64_t n, bool bf16) {
     L.map = L.mask + up256((size_t)lcvq::mask_bytes(m, n));
     L.total = L.map + up256((size_t)lcvq::map_rows(N, n) * 72 * 4);
   } else {
-    L.frag = L.xt = L.dyt = L.mask = L.map = L.total = up256((size_t)N * 4);
+    // the map gradients' per-block partial sums alone
+    L.total = up256((size_t)lcvq::map_rows_f32(m, n) * 72 * 4);
   }
   return L;
 }
@@ -440,10 +441,10 @@ static lcvq_status_t linear_fwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
     save = lcvq::FwdSave{(uint32_t *)(sv + S.frag_t), (uint64_t *)(sv + S.mask_r), (uint64_t *)(sv + S.mask_l),
                          (uint16_t *)(sv + S.xt)};
   }
-  char *ws = (char *)workspace;
-  float *svec = (float *)(ws + L.s);
   hipError_t e;
   if (bf16) {
+    char *ws = (char *)workspace;
+    float *svec = (float *)(ws + L.s);
     uint32_t *frag = (uint32_t *)(ws + L.frag);
     {
       Timed tm(LCVQ_K_FWD_PREP, st);
@@ -455,11 +456,19 @@ static lcvq_status_t linear_fwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
     { Timed tm(LCVQ_K_FWD, st); e = tm.done(lcvq::launch_fwd_bf16(frag, (const uint16_t *)(ws + L.xp), L.ldp, svec, (uint16_t *)Y, N, m, n, st)); }
     if (e != hipSuccess) return hip_fail(e, "forward product launch");
   } else {
-    { Timed tm(LCVQ_K_FWD_PREP, st); e = tm.done(lcvq::launch_act_transform(X, false, N, N, n, d, A, b, ws + L.xp, n, svec, st)); }
-    if (e != hipSuccess) return hip_fail(e, "activation transform launch");
+    const float *Xf = (const float *)X;
+    float *s = nullptr;
+    if (!lcvq::f32_fused_act(N, m, n)) {
+      float *Xp = (float *)((char *)workspace + L.xp);
+      s = (float *)((char *)workspace + L.s);
+      Timed tm(LCVQ_K_FWD_PREP, st);
+      e = tm.done(lcvq::launch_act_f32(Xf, A, b, d, Xp, s, N, n, st));
+      if (e != hipSuccess) return hip_fail(e, "activation transform launch");
+      Xf = Xp;
+    }
     {
       Timed tm(LCVQ_K_FWD, st);
-      e = tm.done(lcvq::launch_fwd_f32((const float *)Z, qz, (const float *)(ws + L.xp), svec, (float *)Y, N, m, n, st));
+      e = tm.done(lcvq::launch_fwd_f32((const float *)Z, qz, Xf, s, A, b, d, (float *)Y, N, m, n, st));
     }
     if (e != hipSuccess) return hip_fail(e, "forward product launch");
     if (packed_codes_out != nullptr) {
@@ -651,9 +660,7 @@ static lcvq_status_t linear_bwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
   if (workspace == nullptr || workspace_bytes < L.total)
     return fail(LCVQ_EWORKSPACE, "workspace %zu bytes, need %zu", workspace_bytes, L.total);
   char *ws = (char *)workspace;
-  float *rs = (float *)(ws + L.rs);
   const bool want_map = dA != nullptr;
-  const bool clear_map = want_map && !accumulate;
 
   if (bf16) {
     // 1. one prepass launch: codes in the input-gradient operand layout (when
@@ -665,6 +672,7 @@ static lcvq_status_t linear_bwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
     //    (the two products are independent; in this order the step measured
     //    slightly shorter)
     const bool run_dx = dX != nullptr || want_map;
+    float *rs = (float *)(ws + L.rs);
     float *mapp = want_map ? (float *)(ws + L.map) : nullptr;
     uint32_t *frag = (uint32_t *)(ws + L.frag);
     uint16_t *xt = (uint16_t *)(ws + L.xt), *dyt = (uint16_t *)(ws + L.dyt);
@@ -715,25 +723,22 @@ static lcvq_status_t linear_bwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
   }
 
   // fp32 mode
-  float *zA = clear_map ? dA : nullptr;
-  float *zb = clear_map ? db : nullptr;
   if (dX != nullptr) {
-    { Timed tm(LCVQ_K_BWD_PREP, st); e = tm.done(lcvq::launch_rowsum(dY, false, N, N, m, rs, zA, zb, d, st)); }
-    if (e != hipSuccess) return hip_fail(e, "row-sum launch");
-    zA = zb = nullptr;  // cleared by the row-sum launch
     Timed tm(LCVQ_K_DX, st);
-    e = tm.done(lcvq::launch_dx_f32((const float *)Z, qz, (const float *)dY, rs, A, b, d, (float *)dX, N, m, n, st));
+    e = tm.done(lcvq::launch_dx_f32((const float *)Z, qz, (const float *)dY, A, b, d, (float *)dX, N, m, n, st));
     if (e != hipSuccess) return hip_fail(e, "input-gradient launch");
   }
-  if (zA != nullptr) {
-    if ((e = fill_zero(zA, (size_t)d * d * 4, st)) != hipSuccess) return hip_fail(e, "zero fill");
-    if ((e = fill_zero(zb, (size_t)d * 4, st)) != hipSuccess) return hip_fail(e, "zero fill");
-  }
+  float *mapp = want_map ? (float *)(ws + L.map) : nullptr;
   if (dZ != nullptr || want_map) {
     Timed tm(LCVQ_K_DW, st);
     e = tm.done(lcvq::launch_dz_f32((const float *)X, (const float *)dY, (const float *)Z, qz, A, d, mask_mode, est,
-                                    accumulate, (float *)dZ, dA, db, N, m, n, st));
+                                    accumulate, (float *)dZ, mapp, N, m, n, st));
     if (e != hipSuccess) return hip_fail(e, "weight-gradient launch");
+  }
+  if (want_map) {
+    Timed tm(LCVQ_K_MAP_SUM, st);
+    e = tm.done(lcvq::launch_map_combine(mapp, lcvq::map_rows_f32(m, n), d, accumulate, dA, db, st));
+    if (e != hipSuccess) return hip_fail(e, "map-gradient sum launch");
   }
   return ok();
 }

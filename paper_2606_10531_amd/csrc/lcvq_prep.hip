@@ -85,17 +85,6 @@ __device__ __forceinline__ void storeD_nt(float *p, const float v[D]) {
   }
 }
 
-__device__ __forceinline__ float block_sum256(float v, float *red /* >= 4 floats of LDS */) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) red[wave] = v;
-  __syncthreads();
-  float t = red[0] + red[1] + red[2] + red[3];
-  __syncthreads();
-  return t;
-}
-
 // ---- quantise into the operand layouts --------------------------------------
 // One block quantises four 64 x 64 tiles of bf16 Z side by side: tile row by
 // (rows r), tile columns 4 bq .. 4 bq + 3 (columns c).  Elements beyond Z are
@@ -261,49 +250,6 @@ __device__ __forceinline__ void quant_block(int bq, int by, int gx, const uint16
   }
 }
 
-// ---- activation transform (def. forward_x), fp32 row-major -----------------
-// One block per token row: X'[t, g*D + k] = sum_j X[t, g*D + j] A[j, k] and
-// s[t] = sum_c X[t, c] b[c % D], X' row-major with row length ldp.
-template <typename XT, typename OT, int D>
-__global__ __launch_bounds__(256) void k_act_transform(const XT *__restrict__ X, int64_t N, int64_t n,
-                                                        const float *__restrict__ A,
-                                                        const float *__restrict__ b,
-                                                        OT *__restrict__ Xp, int64_t ldp,
-                                                        float *__restrict__ s) {
-  __shared__ float red[4];
-  const int64_t t = blockIdx.x;
-  const int64_t G = n / D, GP = ldp / D;
-  float a[D][D], bb[D];
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    bb[j] = b[j];
-#pragma unroll
-    for (int k = 0; k < D; ++k) a[j][k] = A[j * D + k];
-  }
-  float acc_s = 0.0f;
-  for (int64_t g = threadIdx.x; g < GP; g += 256) {
-    float x[D], y[D];
-    if (t < N && g < G) {
-      loadD<D>(X + t * n + g * D, x);
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) x[j] = 0.0f;
-    }
-#pragma unroll
-    for (int k = 0; k < D; ++k) {
-      float v = 0.0f;
-#pragma unroll
-      for (int j = 0; j < D; ++j) v = fmaf(x[j], a[j][k], v);
-      y[k] = v;
-    }
-#pragma unroll
-    for (int j = 0; j < D; ++j) acc_s = fmaf(x[j], bb[j], acc_s);
-    storeD<D>(Xp + t * ldp + g * D, y);
-  }
-  const float tot = block_sum256(acc_s, red);
-  if (threadIdx.x == 0) s[t] = tot;
-}
-
 // ---- backward operands of the weight-gradient product ----------------------
 // Transposed store of one 64-token x 64-feature sub-tile from the LDS tile
 // into the token-K fragment layout of v_mfma_f32_16x16x32_bf16 (zero-padded to
@@ -466,39 +412,6 @@ __global__ __launch_bounds__(256) void k_fwd_prep(const uint16_t *__restrict__ Z
     const int j = id - nq, nbt = (int)(Np / 64);
     act_block<D, kSave>(j % nbt, j / nbt, X, N, n, A, b, Xp, KB, spc, nkc, Np, sp, xt, KBx, (int)(Np / 64),
                         reinterpret_cast<uint16_t (*)[64][64 + 8]>(lds));
-  }
-}
-
-// ---- per-token sums of dY (dX offset term) ---------------------------------
-// rs[t] = sum_r dY[t, r]; rows t in [N, Np) get 0.  Block 0 also clears dA/db
-// when the backward overwrites them.
-template <typename T, bool kVec>
-__global__ __launch_bounds__(256) void k_rowsum(const T *__restrict__ dY, int64_t N, int64_t m,
-                                                 float *__restrict__ rs, float *__restrict__ dA,
-                                                 float *__restrict__ db, int dd) {
-  __shared__ float red[4];
-  const int64_t t = blockIdx.x;
-  float acc = 0.0f;
-  if (t < N) {
-    const T *row = dY + t * m;
-    if constexpr (kVec) {
-      for (int64_t c = (int64_t)threadIdx.x * 8; c < m; c += 256 * 8) {
-        float v[8];
-        load8(row + c, v);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc += v[j];
-      }
-    } else {
-      for (int64_t c = threadIdx.x; c < m; c += 256) {
-        if constexpr (sizeof(T) == 2) acc += bf16_to_f32(row[c]); else acc += (float)row[c];
-      }
-    }
-  }
-  const float tot = block_sum256(acc, red);
-  if (threadIdx.x == 0) rs[t] = tot;
-  if (blockIdx.x == 0 && dA != nullptr) {
-    for (int i = threadIdx.x; i < dd * dd; i += 256) dA[i] = 0.0f;
-    for (int i = threadIdx.x; i < dd; i += 256) db[i] = 0.0f;
   }
 }
 
@@ -924,17 +837,6 @@ static inline int grid_for(int64_t items, int64_t per_block) {
   return (int)(g < 1 ? 1 : g);
 }
 
-hipError_t launch_act_transform(const void *X, bool bf16, int64_t N, int64_t Np, int64_t n, int d,
-                                const float *A, const float *b, void *Xp, int64_t ldp, float *s,
-                                hipStream_t st) {
-  (void)Np;
-  (void)bf16;  // fp32 only: the bf16 transform runs inside launch_fwd_prep_bf16
-  dim3 grid((unsigned)N);
-  if (d == 8) k_act_transform<float, float, 8><<<grid, 256, 0, st>>>((const float *)X, N, n, A, b, (float *)Xp, ldp, s);
-  else k_act_transform<float, float, 4><<<grid, 256, 0, st>>>((const float *)X, N, n, A, b, (float *)Xp, ldp, s);
-  return hipGetLastError();
-}
-
 hipError_t launch_fwd_prep_bf16(const uint16_t *Z, int64_t m, int64_t n, const Quantizer &qz, uint32_t *frag,
                                 uint8_t *packed,
                                 const uint16_t *X, int64_t N, int64_t Np, int64_t ldp, int d, const float *A,
@@ -960,19 +862,6 @@ hipError_t launch_fwd_prep_bf16(const uint16_t *Z, int64_t m, int64_t n, const Q
     else
       k_fwd_prep<4, false><<<grid, 256, 0, st>>>(Z, m, n, qz, frag, packed, gq, nq, X, N, A, b, Xp, KB, spc, nkc, Np, sp,
                                                  nullptr, 0, nullptr, nullptr, 0, nullptr, 0);
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_rowsum(const void *dY, bool bf16, int64_t N, int64_t Np, int64_t m, float *rs, float *dA,
-                         float *db, int d, hipStream_t st) {
-  dim3 grid((unsigned)Np);
-  if (bf16) {
-    if (m % 8 == 0) k_rowsum<uint16_t, true><<<grid, 256, 0, st>>>((const uint16_t *)dY, N, m, rs, dA, db, d);
-    else k_rowsum<uint16_t, false><<<grid, 256, 0, st>>>((const uint16_t *)dY, N, m, rs, dA, db, d);
-  } else {
-    if (m % 8 == 0) k_rowsum<float, true><<<grid, 256, 0, st>>>((const float *)dY, N, m, rs, dA, db, d);
-    else k_rowsum<float, false><<<grid, 256, 0, st>>>((const float *)dY, N, m, rs, dA, db, d);
   }
   return hipGetLastError();
 }

@@ -72,11 +72,6 @@ hipError_t launch_bwd_prep_bf16(const uint16_t *Z, int64_t m, int64_t n, const Q
                                 const uint16_t *X,
                                 const uint16_t *dY, const float *A, int d, int64_t N, uint16_t *xt,
                                 uint16_t *dyt, float *rsp, uint64_t *maskbits, int mask_mode, hipStream_t st);
-hipError_t launch_act_transform(const void *X, bool bf16, int64_t N, int64_t Np, int64_t n, int d,
-                                const float *A, const float *b, void *Xp, int64_t ldp, float *s,
-                                hipStream_t st);
-hipError_t launch_rowsum(const void *dY, bool bf16, int64_t N, int64_t Np, int64_t m, float *rs, float *dA,
-                         float *db, int d, hipStream_t st);
 hipError_t launch_pack2bit(const void *src, int kind, bool bf16, int64_t m, int64_t n, uint8_t *packed,
                            const Quantizer &qz, hipStream_t st);
 hipError_t launch_dequant(const void *src, int kind, bool z_bf16, int64_t m, int64_t n, int d,
@@ -150,13 +145,21 @@ hipError_t launch_dw_bf16(const uint16_t *xt, const uint16_t *dyt, const uint64_
                           const Quantizer &qz, int mask_mode, const GradEst &est, int accumulate, void *dZ,
                           bool dz_bf16, int64_t N, int64_t m, int64_t n, hipStream_t st);
 
-// fp32 products on the vector ALUs (lcvq_f32.hip)
-hipError_t launch_fwd_f32(const float *Z, const Quantizer &qz, const float *Xp, const float *s, float *Y,
-                          int64_t N, int64_t m, int64_t n, hipStream_t st);
-hipError_t launch_dx_f32(const float *Z, const Quantizer &qz, const float *dY, const float *rs, const float *A,
-                         const float *b, int d, float *dX, int64_t N, int64_t m, int64_t n, hipStream_t st);
+// fp32 products (lcvq_f32.hip).  The weight gradient's map_rows_f32(m, n) blocks
+// store their partial sums of dA and db as the bf16 path's input gradient does
+// (mapp may be nullptr), for launch_map_combine.
+int map_rows_f32(int64_t m, int64_t n);
+// Whether the forward takes X itself and transforms it (small layers); else
+// launch_act_f32 makes X' and s first and launch_fwd_f32 takes those (s != nullptr).
+bool f32_fused_act(int64_t N, int64_t m, int64_t n);
+hipError_t launch_act_f32(const float *X, const float *A, const float *b, int d, float *Xp, float *s, int64_t N,
+                          int64_t n, hipStream_t st);
+hipError_t launch_fwd_f32(const float *Z, const Quantizer &qz, const float *X, const float *s, const float *A,
+                          const float *b, int d, float *Y, int64_t N, int64_t m, int64_t n, hipStream_t st);
+hipError_t launch_dx_f32(const float *Z, const Quantizer &qz, const float *dY, const float *A, const float *b, int d,
+                         float *dX, int64_t N, int64_t m, int64_t n, hipStream_t st);
 hipError_t launch_dz_f32(const float *X, const float *dY, const float *Z, const Quantizer &qz, const float *A,
-                         int d, int mask_mode, const GradEst &est, int accumulate, float *dZ, float *dA, float *db,
-                         int64_t N, int64_t m, int64_t n, hipStream_t st);
+                         int d, int mask_mode, const GradEst &est, int accumulate, float *dZ, float *mapp, int64_t N,
+                         int64_t m, int64_t n, hipStream_t st);
 
 }  // namespace lcvq
