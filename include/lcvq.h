@@ -166,8 +166,9 @@ lcvq_status_t lcvq_encode(int64_t m, int64_t n, int32_t d, const void *W, int32_
 /*
  * lcvq_workspace_bytes -- device workspace needed by lcvq_linear_fwd
  * (op = LCVQ_OP_FWD), lcvq_linear_bwd / lcvq_linear_bwd_dge (op = LCVQ_OP_BWD)
- * or lcvq_linear_fwd_packed (op = LCVQ_OP_FWD_PACKED, dtype LCVQ_BF16; the
- * size does not depend on N) for these sizes and element type.  Returns 0 for invalid arguments.  The workspace holds
+ * or lcvq_linear_fwd_packed (op = LCVQ_OP_FWD_PACKED, dtype LCVQ_BF16; it grows
+ * with N above 16 tokens, up to 64 MiB, and a smaller one is accepted, see there)
+ * for these sizes and element type.  Returns 0 for invalid arguments.  The workspace holds
  * transient, library-private data (transformed activations, codes in the
  * matrix-core operand layout, per-token sums, partial sums of dA and db); its
  * contents are undefined between calls.
@@ -214,15 +215,18 @@ lcvq_status_t lcvq_linear_fwd_ex(int64_t N, int64_t m, int64_t n, int32_t d, int
  * lcvq_linear_fwd_packed -- Y = X W_hat^T with the codes read from their packed
  * 2-bit form (lcvq_pack2bit layout): inference with the compressed weight
  * (def. forward_x, Sec. 3.2, evaluated as in the paper's inference kernel of
- * App. A.2 without ever forming W_hat).  For decode-sized batches: tokens are
- * processed 16 at a time, and the packed codes (m * n / 4 bytes, the only
- * large operand) are streamed once per 16 tokens.
+ * App. A.2 without ever forming W_hat).  Up to 16 tokens are one pass over the
+ * packed codes (m * n / 4 bytes, the only large operand); more are taken in as few
+ * passes as the workspace allows (2 n bytes per token, whole 64-token tiles), with
+ * the same bits whatever the number of passes, or 16 at a time when it holds fewer
+ * than 64 tokens.
  *   N, m, n    tokens, out-features, in-features; d in {4, 8}
  *   packed     m * n / 4 bytes of codes (device, 16-byte aligned)
  *   A, b       map and offset, fp32 (device)
  *   X          N x n bf16 activations;  Y  N x m output of element type y_dtype
  *              (LCVQ_BF16 or LCVQ_F32), written
- *   workspace  at least lcvq_workspace_bytes(LCVQ_OP_FWD_PACKED, N, m, n, d, LCVQ_BF16)
+ *   workspace  at least lcvq_workspace_bytes(LCVQ_OP_FWD_PACKED, 1, m, n, d, LCVQ_BF16),
+ *              best ... (LCVQ_OP_FWD_PACKED, N, ...)
  * Requires n % 64 == 0 and m % 8 == 0 (else LCVQ_EUNSUPPORTED).  X' = X
  * blockdiag(A) is rounded to bf16 as in lcvq_linear_fwd.  Calls that share a
  * workspace must not run concurrently (it holds per-call tile counters).

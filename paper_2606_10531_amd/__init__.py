@@ -257,7 +257,10 @@ def linear_fwd(Z: torch.Tensor, A: torch.Tensor, b: torch.Tensor, X: torch.Tenso
 def linear_fwd_packed(packed: torch.Tensor, A: torch.Tensor, b: torch.Tensor, X: torch.Tensor, d: int,
                       out_dtype: torch.dtype = torch.bfloat16, workspace: torch.Tensor | None = None,
                       out: torch.Tensor | None = None) -> torch.Tensor:
-    """Y = X W_hat^T (N x m, bf16 or fp32) from packed 2-bit codes (m x n/4 uint8) and bf16 X (N x n)."""
+    """Y = X W_hat^T (N x m, bf16 or fp32) from packed 2-bit codes (m x n/4 uint8) and bf16 X (N x n).
+
+    A workspace of workspace_bytes(OP_FWD_PACKED, N, ...) takes all N tokens in as few passes as
+    it can; any workspace sized for one token is accepted."""
     m, n4 = _check_2d(packed, "packed")
     n = 4 * n4
     _check(packed, "packed", dtype=torch.uint8)
@@ -268,7 +271,8 @@ def linear_fwd_packed(packed: torch.Tensor, A: torch.Tensor, b: torch.Tensor, X:
         _check(out, "out", (N, m), (torch.float32, torch.bfloat16))
     else:
         out = torch.empty((N, m), dtype=out_dtype, device=X.device)
-    ws = _workspace(OP_FWD_PACKED, N, m, n, d, torch.bfloat16, X.device, workspace)
+    # a workspace for one token will do; one for N tokens needs the fewest passes
+    ws = _workspace(OP_FWD_PACKED, N if workspace is None else 1, m, n, d, torch.bfloat16, X.device, workspace)
     _lib.check(_lib.load().lcvq_linear_fwd_packed(N, m, n, d, _dev(packed, "packed"), _dev(A, "A"), _dev(b, "b"),
                                                   _dev(X, "X"), _dev(out, "Y"), _DT[out.dtype],
                                                   _dev(ws, "workspace"), ws.numel(), _stream(X.device)),

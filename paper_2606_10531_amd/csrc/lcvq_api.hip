@@ -280,7 +280,10 @@ size_t lcvq_workspace_bytes(int32_t op, int64_t N, int64_t m, int64_t n, int32_t
   const bool bf16 = dtype == LCVQ_BF16;
   if (op == LCVQ_OP_FWD) return fwd_layout(N, m, n, bf16).total;
   if (op == LCVQ_OP_BWD) return bwd_layout(N, m, n, bf16).total;
-  if (op == LCVQ_OP_FWD_PACKED) return bf16 ? packed_layout(m, n).total : 0;
+  if (op == LCVQ_OP_FWD_PACKED) {
+    if (!bf16) return 0;
+    return std::max(packed_layout(m, n).total, (size_t)lcvq::packed_wide_plan(N, n, lcvq::kPackedWideBytes).bytes);
+  }
   return 0;
 }
 
@@ -535,6 +538,22 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
   uint16_t *xq = (uint16_t *)(ws + L.xq);
   float *sp = (float *)(ws + L.sp), *part = (float *)(ws + L.part);
   int *counters = (int *)(ws + L.counters);
+  const lcvq::PackedWidePlan wide =
+      lcvq::packed_wide_plan(N, n, (int64_t)std::min<size_t>(workspace_bytes, (size_t)lcvq::kPackedWideBytes));
+  if (wide.T > 0) {
+    for (int64_t t0 = 0; t0 < N; t0 += wide.T) {
+      const int Nc = (int)std::min<int64_t>(wide.T, N - t0);
+      {
+        Timed tm(LCVQ_K_PACKED_PREP, st);
+        e = tm.done(lcvq::launch_packed_wide_prep(wide, (const uint16_t *)X + t0 * n, Nc, n, d, A, b, ws, st));
+        if (e != hipSuccess) return hip_fail(e, "packed prepass launch");
+      }
+      Timed tm(LCVQ_K_PACKED, st);
+      e = tm.done(lcvq::launch_packed_wide(wide, packed, m, n, ws, Nc, (char *)Y + t0 * m * ys, y_dtype == LCVQ_BF16, st));
+      if (e != hipSuccess) return hip_fail(e, "packed product launch");
+    }
+    return ok();
+  }
   for (int64_t t0 = 0; t0 < N; t0 += 16) {
     const int Nc = (int)std::min<int64_t>(16, N - t0);
     if (lcvq::packed_fused(m, n, Nc)) {  // the product block computes its own X'' and s

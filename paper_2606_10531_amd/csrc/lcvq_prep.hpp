@@ -105,6 +105,21 @@ bool packed_fused(int64_t m, int64_t n, int Nc);
 hipError_t launch_packed_fused(const uint8_t *packed, int64_t m, int64_t n, const uint16_t *X, int Nc, int d,
                                const float *A, const float *b, void *Y, bool y_bf16, hipStream_t st);
 
+// The same for more than 16 tokens, T tokens per pass (lcvq_packed_wide.hip); T = 0:
+// not used (few tokens, or `bytes` of workspace do not hold 64 tokens' X').  The
+// workspace holds X' of a pass and, at byte sp, `parts` rows of T partial sums of s.
+// lcvq_workspace_bytes asks for one pass of all tokens up to kPackedWideBytes.
+constexpr int64_t kPackedWideBytes = (int64_t)64 << 20;
+struct PackedWidePlan {
+  int T, KT, spp, parts;  // tokens per pass, 256-wide steps, steps per part, parts of s
+  int64_t sp, bytes;
+};
+PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes);
+hipError_t launch_packed_wide_prep(const PackedWidePlan &p, const uint16_t *X, int Nc, int64_t n, int d, const float *A,
+                                   const float *b, char *ws, hipStream_t st);
+hipError_t launch_packed_wide(const PackedWidePlan &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc,
+                              void *Y, bool y_bf16, hipStream_t st);
+
 // LC encode (lcvq_encode.hip): codes (m x n bytes) and / or packed codes of a dense weight
 hipError_t launch_encode(const void *W, bool w_bf16, int64_t m, int64_t n, int d, const float *A, const float *b,
                          uint8_t *codes, uint8_t *packed, hipStream_t st);
