@@ -229,7 +229,7 @@ lcvq_status_t lcvq_linear_fwd_ex(int64_t N, int64_t m, int64_t n, int32_t d, int
  *              best ... (LCVQ_OP_FWD_PACKED, N, ...)
  * Requires n % 64 == 0 and m % 8 == 0 (else LCVQ_EUNSUPPORTED).  X' = X
  * blockdiag(A) is rounded to bf16 as in lcvq_linear_fwd.  Calls that share a
- * workspace must not run concurrently (it holds per-call tile counters).
+ * workspace must not run concurrently (it holds X' and s of the call).
  */
 lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d, const uint8_t *packed,
                                      const float *A, const float *b, const void *X, void *Y, int32_t y_dtype,
@@ -251,7 +251,7 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
  *     looked up for the current device).
  *   - All calls on one device share that device's array: calls that overlap in
  *     time on one device (different streams, or host threads) race and give
- *     wrong results.  What must start at zero is cleared by each call.
+ *     wrong results.
  */
 lcvq_status_t lcvq_linear_fwd_packed_noalloc(int64_t N, int64_t m, int64_t n, int32_t d, const uint8_t *packed,
                                              const float *A, const float *b, const void *X, void *Y,

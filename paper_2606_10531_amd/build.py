@@ -23,7 +23,7 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # The products' epilogues issue matrix-core instructions through the compiler's
 # builtins, accumulating in vector registers (the accumulator registers hold the
 # main loop's results): select the vector-register form for them.
-PER_FILE_FLAGS = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form=true"] for s in ("lcvq_gemm.hip", "lcvq_split.hip")}
+PER_FILE_FLAGS = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form=true"] for s in ("lcvq_gemm.hip", "lcvq_split.hip", "lcvq_packed.hip")}
 
 
 def hipcc() -> str:

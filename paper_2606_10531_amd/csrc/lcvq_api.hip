@@ -123,22 +123,6 @@ SavedLayout saved_layout(int64_t N, int64_t m, int64_t n) {
   return L;
 }
 
-// Layer output from packed codes: X' of 16 tokens, partial s, split-K
-// partials of the product and its tile counters.
-struct PackedLayout {
-  size_t xq, sp, part, counters, total;
-};
-PackedLayout packed_layout(int64_t m, int64_t n) {
-  const lcvq::PackedPlan p = lcvq::packed_plan(m, n);
-  PackedLayout L{};
-  L.xq = 0;
-  L.sp = up256((size_t)16 * p.nP * 2);
-  L.part = L.sp + up256((size_t)p.nchunks * 16 * 4);
-  L.counters = L.part + up256(p.KS > 1 ? (size_t)p.row_tiles * p.KS * 16 * 64 * 4 : 0);
-  L.total = L.counters + up256((size_t)p.row_tiles * 4);
-  return L;
-}
-
 // ---- per-kernel event timing (instrumentation, off by default) ------------
 struct Timer {
   std::atomic<uint32_t> mask{0};
@@ -282,7 +266,7 @@ size_t lcvq_workspace_bytes(int32_t op, int64_t N, int64_t m, int64_t n, int32_t
   if (op == LCVQ_OP_BWD) return bwd_layout(N, m, n, bf16).total;
   if (op == LCVQ_OP_FWD_PACKED) {
     if (!bf16) return 0;
-    return std::max(packed_layout(m, n).total, (size_t)lcvq::packed_wide_plan(N, n, lcvq::kPackedWideBytes).bytes);
+    return up256((size_t)std::max(lcvq::packed_narrow(n).bytes, lcvq::packed_wide_plan(N, n, lcvq::kPackedWideBytes).bytes));
   }
   return 0;
 }
@@ -531,13 +515,10 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
     return fail(LCVQ_EINVAL, "null required pointer (packed, A, b, X)");
   if (!aligned16(packed) || !aligned16(X) || !aligned16(workspace))
     return fail(LCVQ_EALIGN, "packed, X and workspace must be 16-byte aligned");
-  const PackedLayout L = packed_layout(m, n);
-  if (workspace == nullptr || workspace_bytes < L.total)
-    return fail(LCVQ_EWORKSPACE, "workspace %zu bytes, need %zu", workspace_bytes, L.total);
+  const lcvq::PackedNarrow narrow = lcvq::packed_narrow(n);
+  if (workspace == nullptr || workspace_bytes < (size_t)narrow.bytes)
+    return fail(LCVQ_EWORKSPACE, "workspace %zu bytes, need %zu", workspace_bytes, (size_t)narrow.bytes);
   char *ws = (char *)workspace;
-  uint16_t *xq = (uint16_t *)(ws + L.xq);
-  float *sp = (float *)(ws + L.sp), *part = (float *)(ws + L.part);
-  int *counters = (int *)(ws + L.counters);
   const lcvq::PackedWidePlan wide =
       lcvq::packed_wide_plan(N, n, (int64_t)std::min<size_t>(workspace_bytes, (size_t)lcvq::kPackedWideBytes));
   if (wide.T > 0) {
@@ -545,7 +526,8 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
       const int Nc = (int)std::min<int64_t>(wide.T, N - t0);
       {
         Timed tm(LCVQ_K_PACKED_PREP, st);
-        e = tm.done(lcvq::launch_packed_wide_prep(wide, (const uint16_t *)X + t0 * n, Nc, n, d, A, b, ws, st));
+        e = tm.done(lcvq::launch_packed_xprep((const uint16_t *)X + t0 * n, Nc, n, wide.KT, wide.spp, wide.parts, d, A, b,
+                                              (uint16_t *)ws, (float *)(ws + wide.sp), wide.T, st));
         if (e != hipSuccess) return hip_fail(e, "packed prepass launch");
       }
       Timed tm(LCVQ_K_PACKED, st);
@@ -556,21 +538,22 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
   }
   for (int64_t t0 = 0; t0 < N; t0 += 16) {
     const int Nc = (int)std::min<int64_t>(16, N - t0);
-    if (lcvq::packed_fused(m, n, Nc)) {  // the product block computes its own X'' and s
+    const uint16_t *Xc = (const uint16_t *)X + t0 * n;
+    char *Yc = (char *)Y + t0 * m * ys;
+    if (lcvq::packed_fused(Nc)) {  // the product transforms X itself
       Timed tm(LCVQ_K_PACKED, st);
-      e = tm.done(lcvq::launch_packed_fused(packed, m, n, (const uint16_t *)X + t0 * n, Nc, d, A, b,
-                                            (char *)Y + t0 * m * ys, y_dtype == LCVQ_BF16, st));
+      e = tm.done(lcvq::launch_packed_fused(narrow, packed, m, n, Xc, Nc, d, A, b, Yc, y_dtype == LCVQ_BF16, st));
       if (e != hipSuccess) return hip_fail(e, "packed product launch");
       continue;
     }
     {
       Timed tm(LCVQ_K_PACKED_PREP, st);
-      e = tm.done(lcvq::launch_packed_prep((const uint16_t *)X + t0 * n, Nc, m, n, d, A, b, xq, sp, counters, st));
+      e = tm.done(lcvq::launch_packed_xprep(Xc, Nc, n, narrow.KT, narrow.spp, narrow.parts, d, A, b, (uint16_t *)ws,
+                                            (float *)(ws + narrow.sp), 16, st));
       if (e != hipSuccess) return hip_fail(e, "packed prepass launch");
     }
     Timed tm(LCVQ_K_PACKED, st);
-    e = tm.done(lcvq::launch_packed_gemv(packed, m, n, xq, sp, Nc, part, counters, (char *)Y + t0 * m * ys,
-                                         y_dtype == LCVQ_BF16, st));
+    e = tm.done(lcvq::launch_packed(narrow, packed, m, n, ws, Nc, Yc, y_dtype == LCVQ_BF16, st));
     if (e != hipSuccess) return hip_fail(e, "packed product launch");
   }
   return ok();
@@ -579,10 +562,8 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
 }  // extern "C"
 
 // ---- scratch of the allocation-free packed forward --------------------------
-// A fixed device array takes the place of the workspace argument: X'' of 16
-// tokens, the partial sums of s, the split-K partial tiles and the tile
-// counters (which the prepass zeroes on every call).  Each device that runs the
-// call holds its own copy until the process ends; in host code `scratch` is
+// A fixed device array takes the place of the workspace argument: X' of a pass
+// and the partial sums of s.  Each device that runs the call holds its own copy until the process ends; in host code `scratch` is
 // only a stand-in for the symbol, so its device address is looked up once per
 // device (hipGetSymbolAddress, with that device current) and only that address
 // is ever passed to kernels.
@@ -621,9 +602,9 @@ lcvq_status_t lcvq_linear_fwd_packed_noalloc(int64_t N, int64_t m, int64_t n, in
                                              const float *A, const float *b, const void *X, void *Y,
                                              int32_t y_dtype, void *stream) {
   // the size check needs no device: reject before touching the runtime
-  if (m > 0 && n > 0 && m < kMaxLd && n < kMaxLd && n % 64 == 0 && packed_layout(m, n).total > kScratchBytes)
+  if (m > 0 && n > 0 && m < kMaxLd && n < kMaxLd && n % 64 == 0 && (size_t)lcvq::packed_narrow(n).bytes > kScratchBytes)
     return fail(LCVQ_EUNSUPPORTED, "m=%lld n=%lld needs %zu bytes of scratch, the static array holds %zu",
-                (long long)m, (long long)n, packed_layout(m, n).total, kScratchBytes);
+                (long long)m, (long long)n, (size_t)lcvq::packed_narrow(n).bytes, kScratchBytes);
   void *ws = nullptr;
   if (N > 0 && m > 0 && n > 0) {
     const lcvq_status_t s = scratch_of_current_device(&ws);

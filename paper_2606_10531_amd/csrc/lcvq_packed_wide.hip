@@ -273,12 +273,11 @@ PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes) {
   return p;
 }
 
-hipError_t launch_packed_wide_prep(const PackedWidePlan &p, const uint16_t *X, int Nc, int64_t n, int d, const float *A,
-                                   const float *b, char *ws, hipStream_t st) {
-  const dim3 g((unsigned)ceil_div(Nc, 16), (unsigned)p.parts);
-  const unsigned threads = 256u * (unsigned)(p.spp < 4 ? p.spp : 4);
-  (d == 8 ? k_packed_xprep<8> : k_packed_xprep<4>)<<<g, threads, 0, st>>>(X, Nc, n, p.KT, p.spp, A, b, (uint16_t *)ws,
-                                                                      (float *)(ws + p.sp), p.T);
+hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int spp, int parts, int d, const float *A,
+                               const float *b, uint16_t *xq, float *sp, int Tp, hipStream_t st) {
+  const dim3 g((unsigned)ceil_div(Nc, 16), (unsigned)parts);
+  const unsigned threads = 256u * (unsigned)(spp < 4 ? spp : 4);
+  (d == 8 ? k_packed_xprep<8> : k_packed_xprep<4>)<<<g, threads, 0, st>>>(X, Nc, n, KT, spp, A, b, xq, sp, Tp);
   return hipGetLastError();
 }
 

@@ -81,30 +81,23 @@ hipError_t launch_dequant(const void *src, int kind, bool z_bf16, int64_t m, int
 hipError_t launch_decode_scalar(const void *src, int kind, int64_t total, float scale, float shift, void *W,
                                 bool out_bf16, hipStream_t st);
 
-// layer output from packed 2-bit codes, 16 tokens per pass (lcvq_packed.hip)
-struct PackedPlan {
-  int64_t nP;     // K padded to whole 256-column steps
-  int KT;         // steps
-  int row_tiles;  // 64-row tiles
-  int nchunks;    // 4096-column chunks of the prepass (partial sums of s)
-  int KS, spb;    // K splits over blocks, steps per split
+// layer output from packed 2-bit codes, up to 16 tokens per pass (lcvq_packed.hip).
+// The workspace holds X' of 16 tokens and, at byte sp, `parts` rows of 16 partial
+// sums of s; packed_fused says when the product needs neither (it transforms X
+// itself).
+struct PackedNarrow {
+  int KT, spp, parts;  // 256-wide steps, steps per part, parts of s
+  int64_t sp, bytes;
 };
-PackedPlan packed_plan(int64_t m, int64_t n);
-// X' (16 x nP bf16, columns reordered per 16-column group), partial s
-// (nchunks x 16 fp32) and zeroed tile counters (row_tiles ints) for tokens
-// 0 .. Nc - 1 of X (Nc <= 16)
-hipError_t launch_packed_prep(const uint16_t *X, int Nc, int64_t m, int64_t n, int d, const float *A,
-                              const float *b, uint16_t *xq, float *sp, int *counters, hipStream_t st);
-// Y (Nc x m, bf16 or fp32) = codes X'^T + s; part holds row_tiles * KS * 16 * 64 fp32 split-K partials
-hipError_t launch_packed_gemv(const uint8_t *packed, int64_t m, int64_t n, const uint16_t *xq, const float *sp,
-                              int Nc, float *part, int *counters, void *Y, bool y_bf16, hipStream_t st);
-// Whether the product for Nc tokens runs as one launch that also does the
-// prepass (one block per row tile, few tokens, long rows); then
-// launch_packed_fused replaces launch_packed_prep + launch_packed_gemv.
-bool packed_fused(int64_t m, int64_t n, int Nc);
-hipError_t launch_packed_fused(const uint8_t *packed, int64_t m, int64_t n, const uint16_t *X, int Nc, int d,
-                               const float *A, const float *b, void *Y, bool y_bf16, hipStream_t st);
-
+PackedNarrow packed_narrow(int64_t n);
+bool packed_fused(int Nc);
+// X' in operand order and the parts of s (rows of Tp) for tokens 0 .. Nc - 1
+hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int spp, int parts, int d, const float *A,
+                               const float *b, uint16_t *xq, float *sp, int Tp, hipStream_t st);
+hipError_t launch_packed(const PackedNarrow &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc, void *Y,
+                         bool y_bf16, hipStream_t st);
+hipError_t launch_packed_fused(const PackedNarrow &p, const uint8_t *packed, int64_t m, int64_t n, const uint16_t *X, int Nc,
+                               int d, const float *A, const float *b, void *Y, bool y_bf16, hipStream_t st);
 // The same for more than 16 tokens, T tokens per pass (lcvq_packed_wide.hip); T = 0:
 // not used (few tokens, or `bytes` of workspace do not hold 64 tokens' X').  The
 // workspace holds X' of a pass and, at byte sp, `parts` rows of T partial sums of s.
@@ -115,8 +108,6 @@ struct PackedWidePlan {
   int64_t sp, bytes;
 };
 PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes);
-hipError_t launch_packed_wide_prep(const PackedWidePlan &p, const uint16_t *X, int Nc, int64_t n, int d, const float *A,
-                                   const float *b, char *ws, hipStream_t st);
 hipError_t launch_packed_wide(const PackedWidePlan &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc,
                               void *Y, bool y_bf16, hipStream_t st);
 

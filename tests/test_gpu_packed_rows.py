@@ -1,0 +1,47 @@
+"""The packed-codes forward up to 16 tokens on each of its blocks (16 to 128 rows, 8
+and 16 waves, one and two rounds of blocks), with X transformed in the block (up to 2, up to 4 tokens) and by the
+prepass (5 and more), at ragged rows and K not a multiple of a step, with fewer steps
+than waves and with several per wave, against the oracle at 2e-2; a repeated call
+gives the same bits."""
+import numpy as np
+import pytest
+
+import oracle as orc
+import synth
+from helpers import assert_close, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lc():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2606_10531_amd as lc
+    lc._lib.load()
+    return lc
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 16])
+@pytest.mark.parametrize("m,n,d", [(24, 4160, 8), (72, 8256, 4), (5448, 320, 4), (5448, 6208, 8), (10888, 448, 8),
+                                   (16360, 64, 4), (18440, 192, 8), (22536, 320, 8), (28664, 576, 4),
+                                   (32760, 448, 8), (32776, 128, 8)])
+def test_packed_rows(lc, N, m, n, d):
+    import torch
+    print(f"\npacked rows N={N} m={m} n={n} d={d}", flush=True)
+    r = synth.rng(N + m + n + d)
+    P = r.integers(0, 256, size=(m, n // 4), dtype=np.uint8)
+    Xb = synth.draw_activations(N, n, 7 + N, "bf16")
+    A, b = synth.draw_map(d, 1)
+    Pd, X = torch.from_numpy(P).cuda(), to_dev(Xb, "bf16")
+    Ad, bd = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    need = lc.workspace_bytes(lc.OP_FWD_PACKED, N, m, n, d, torch.bfloat16)
+    got = []
+    for _ in range(2):
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")    # NaN wherever nothing is written
+        Y = torch.full((N, m), float("nan"), dtype=torch.float32, device="cuda")
+        got.append(lc.linear_fwd_packed(Pd, Ad, bd, X, d, workspace=ws, out=Y))
+    torch.cuda.synchronize()
+    ref = orc.linear_forward_packed(P, A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
+    assert_close(to_host(got[0]), ref, 2e-2, "Y")
+    assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
