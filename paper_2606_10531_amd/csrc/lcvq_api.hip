@@ -35,7 +35,7 @@ lcvq_status_t hip_fail(hipError_t e, const char *what) {
 
 bool aligned16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 // quantiser of the code domain: codes = clip(round(Z), 0, 3), gradient factor 1
-constexpr lcvq::Quantizer kCodeDomain{0, 1.0f, 0.0f};
+constexpr lcvq::Quantizer kCodeDomain{1.0f, 0.0f};
 size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Largest row length of an operand streamed through the 256-row tiles with
@@ -467,12 +467,12 @@ static lcvq_status_t linear_fwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
   return ok();
 }
 
-// The quantiser of the `_ex` entry points: (1, 0) is the code domain itself.
+// The quantiser of the `_ex` entry points: (1, 0) is the code domain.
 static lcvq_status_t make_quantizer(float q_scale, float q_shift, lcvq::Quantizer *qz) {
   if (!std::isfinite(q_scale) || !std::isfinite(q_shift) || q_scale == 0.0f)
     return fail(LCVQ_EINVAL, "quantiser scale=%g shift=%g (need finite values, scale != 0)", (double)q_scale,
                 (double)q_shift);
-  *qz = (q_scale == 1.0f && q_shift == 0.0f) ? kCodeDomain : lcvq::Quantizer{1, q_scale, q_shift};
+  *qz = lcvq::Quantizer{q_scale, q_shift};
   return LCVQ_OK;
 }
 

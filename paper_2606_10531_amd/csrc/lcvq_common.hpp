@@ -39,28 +39,56 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 }
 
 // ---- the quantiser of eq. quant_param ------------------------------------
-// code = clip(rint(z), 0, 3); rint is round-half-to-even (v_rndne_f32).
-// fmaxf(NaN, 0) = 0, so a NaN latent gives code 0.
-__device__ __forceinline__ uint32_t quant_code(float z) {
-  float u = __builtin_rintf(z);
-  return (uint32_t)fminf(fmaxf(u, 0.0f), (float)kMaxCode);
+// code = clip(rint(z), 0, 3), rint round-half-to-even.  v_med3_f32 gives 0 for a quiet
+// NaN (rint makes a signalling one quiet).  As a byte: v_cvt_pk_u8_f32 rounds half to
+// even, puts the byte in place and gives 0 for any NaN; clamping before it gives the
+// same code, since the bounds are integers.
+__device__ __forceinline__ float code_clamp(float z) { return __builtin_amdgcn_fmed3f(z, 0.0f, (float)kMaxCode); }
+__device__ __forceinline__ float quant_code_f(float z) { return code_clamp(__builtin_rintf(z)); }
+__device__ __forceinline__ uint32_t quant_code(float z) { return (uint32_t)quant_code_f(z); }
+// Four codes as the bytes of a word.
+__device__ __forceinline__ uint32_t quant_bytes(float z0, float z1, float z2, float z3) {
+  uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(code_clamp(z0), 0, 0u);
+  w = __builtin_amdgcn_cvt_pk_u8_f32(code_clamp(z1), 1, w);
+  w = __builtin_amdgcn_cvt_pk_u8_f32(code_clamp(z2), 2, w);
+  return __builtin_amdgcn_cvt_pk_u8_f32(code_clamp(z3), 3, w);
+}
+// Eight codes as bytes (lo: 0..3, hi: 4..7) -> eight nibbles, and -> 2-bit fields (16
+// bits), code i the i-th from the least significant end.
+__device__ __forceinline__ uint32_t bytes_to_nibbles(uint32_t lo, uint32_t hi) {
+  return __builtin_amdgcn_perm(hi | (hi >> 4), lo | (lo >> 4), 0x06040200u);
+}
+__device__ __forceinline__ uint32_t bytes_to_2bit(uint32_t lo, uint32_t hi) {
+  const uint32_t x = lo | (lo >> 6), y = hi | (hi >> 6);
+  return __builtin_amdgcn_perm(y | (y >> 12), x | (x >> 12), 0x0c0c0400u);
 }
 // Straight-through mask: mode 0 "rounded" (0 <= rint(z) <= 3), mode 1 "latent".
 __device__ __forceinline__ bool ste_pass(float z, int mode) {
   float v = mode == 0 ? __builtin_rintf(z) : z;
   return v >= 0.0f && v <= (float)kMaxCode;
 }
+// The same as an interval [lo, hi]: rint(z) >= 0 from -0.5 (a tie, to -0) on, rint(z) <= 3
+// below 3.5 (a tie, to 4).
+struct MaskRange {
+  float lo, hi;
+};
+__device__ __forceinline__ MaskRange mask_range(int mode) {
+  return mode == 0 ? MaskRange{-0.5f, 3.49999976158142089844f} : MaskRange{0.0f, (float)kMaxCode};
+}
+// bits = 2 bits + (z in the range): inside, the clamp leaves z as it is (a NaN equals
+// nothing); the comparison goes in as the carry.
+__device__ __forceinline__ void mask_push(uint32_t &bits, float z, const MaskRange &r) {
+  const float c = __builtin_amdgcn_fmed3f(z, r.lo, r.hi);
+  asm("v_cmp_eq_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(c), "v"(z) : "vcc");
+}
 
-// Quantiser domain (Sec. 3.4): the quantiser rounds fp32 fma(w, scale, shift);
-// in the code domain (affine = 0) it rounds w itself, bit for bit.  The latent's
-// gradient gains the factor `scale` (1 in the code domain).
+// Quantiser domain (Sec. 3.4): the quantiser rounds fp32 fma(w, scale, shift).  In the
+// code domain that is fma(w, 1, 0), i.e. w itself (-0 becomes +0, with the same code
+// and mask).  The latent's gradient gains the factor `scale`.
 struct Quantizer {
-  int affine;
   float scale, shift;
 };
-__device__ __forceinline__ float code_value(float w, const Quantizer &q) {
-  return q.affine ? fmaf(w, q.scale, q.shift) : w;
-}
+__device__ __forceinline__ float code_value(float w, const Quantizer &q) { return fmaf(w, q.scale, q.shift); }
 
 // Gradient estimator of the latent: straight-through (dge = 0), or the
 // differentiable estimator of eq. dge (Sec. 3.3) with delta = 1, slope

@@ -34,12 +34,11 @@ constexpr int kLdM = kFM + 4;       // LDS row (one k) of an M-contiguous operan
 // MFMA row of weight-side row `r` of a slab (the inverse of slab_row)
 __device__ __forceinline__ int slab_pos(int r) { return 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3); }
 
-// Four codes as floats.  fma with (1, 0) leaves the code domain's values as they are.
+// Four codes as floats.
 __device__ __forceinline__ floatx4 codes4(const floatx4 &z, const Quantizer &qz) {
   floatx4 c;
 #pragma unroll
-  for (int e = 0; e < 4; ++e)
-    c[e] = fminf(fmaxf(__builtin_rintf(fmaf(z[e], qz.scale, qz.shift)), 0.0f), (float)kMaxCode);
+  for (int e = 0; e < 4; ++e) c[e] = quant_code_f(code_value(z[e], qz));
   return c;
 }
 
@@ -344,7 +343,7 @@ __global__ __launch_bounds__(256) void k_f32(const float *__restrict__ Z, Quanti
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const float z = code_value(zv[e], qz);
-          code[4 * h + e] = (float)quant_code(z);
+          code[4 * h + e] = quant_code_f(z);
           const int g = (4 * h + e) / D, k = (4 * h + e) % D;
           float x = 0.0f;
 #pragma unroll

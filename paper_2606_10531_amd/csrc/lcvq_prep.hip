@@ -87,13 +87,20 @@ __device__ __forceinline__ void storeD_nt(float *p, const float v[D]) {
 
 // ---- quantise into the operand layouts --------------------------------------
 // One block quantises four 64 x 64 tiles of bf16 Z side by side: tile row by
-// (rows r), tile columns 4 bq .. 4 bq + 3 (columns c).  Elements beyond Z are
-// quantised from 0 (their products meet zero operands or are not stored).  All
-// loads of the four tiles are issued before the first is used.  What it writes
-// depends on kMode:
+// (rows r), tile columns 4 bq .. 4 bq + 3 (columns c), one tile per wave.  Elements
+// beyond Z are quantised from 0 (their products meet zero operands or are not
+// stored).  All loads of the tile are issued before the first is used.  Lane 4 i + p
+// takes rows slab_row(i) and slab_row(16 + i) of each 32-row slab at columns 8 p and
+// 32 + 8 p: neighbouring lanes read neighbouring memory, a lane's four words are its
+// whole 16 bytes of the forward operand, and the four lanes of a quad hold the four
+// bytes of each mask word and 64 contiguous bits of the packed row, which they put
+// together and store one row block and K half each.  (Before, a
+// thread made 32 stores of one word and 25 vector instructions per latent instead of
+// 17: the saved-state prepass took 232 us at 28672 x 8192 and 4096 tokens, now 202, the
+// copy rate, and 21.1 us at 4096 x 4096 and 256 tokens, now 17.2.)
+// What it writes depends on kMode:
 //   kQuantFwd   the forward product's operand (M axis r, K axis c; tiles at or
-//               past gx skipped), each thread's eight codes stored as one
-//               operand dword, and with `packed` the 2-bit codes;
+//               past gx skipped), and with `packed` the 2-bit codes;
 //   kQuantBwd   the input-gradient product's operand (M axis c, K axis r, rows
 //               of KBt 64-wide steps), through the LDS tiles `codes`, and with
 //               `maskbits` the straight-through mask of mask_mode;
@@ -129,96 +136,98 @@ __device__ __forceinline__ void quant_block(int bq, int by, int gx, const uint16
                                             uint64_t *__restrict__ maskbits = nullptr, int64_t nbc = 0,
                                             int mask_mode = 0, uint64_t *__restrict__ maskbits2 = nullptr) {
   constexpr bool kFwd = kMode != kQuantBwd, kTrans = kMode != kQuantFwd;
-  const int tid = threadIdx.x;
-  const int64_t r0 = (int64_t)by * 64;
-  u32x4 v[4][2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = lane & 3, i16 = lane >> 2;
+  const int64_t r0 = (int64_t)by * 64, bx = 4 * bq + wave;  // the wave's tile
+  const int row16 = 8 * (i16 >> 2) + (i16 & 3);             // slab_row(i16); + 4 for MFMA row 16 + i16
+  u32x4 v[2][2][2];  // [slab][row block][K half]
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int id = tid + 256 * i, rr = id >> 3, cc = (id & 7) * 8;
-      const int64_t r = r0 + rr, c = (int64_t)(4 * bq + q) * 64 + cc;
-      v[q][i] = u32x4{0u, 0u, 0u, 0u};
-      if (r < m && c < n) v[q][i] = *reinterpret_cast<const u32x4 *>(Z + r * n + c);
-    }
-  // straight-through mask of the eight latents of (q, i) -> byte (cc / 8) of
-  // word q of the row in the block's bitmap tile; threads cc / 8 = 0 and 4
-  // store the two halves
-  auto store_mask = [&](int q, int i, uint64_t *__restrict__ bits, int mode) {
-    const int id = tid + 256 * i, rr = id >> 3, cc = (id & 7) * 8;
-    const int64_t r = r0 + rr, c = (int64_t)(4 * bq + q) * 64 + cc;
-    uint32_t mb = 0;
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const bool in = r < m && c + 2 * e < n;
-      mb |= (in && ste_pass(code_value(bf16_lo(v[q][i][e]), qz), mode) ? 1u : 0u) << (2 * e);
-      mb |= (in && ste_pass(code_value(bf16_hi(v[q][i][e]), qz), mode) ? 1u : 0u) << (2 * e + 1);
-    }
-    mb <<= 8 * (id & 3);
-    mb |= (uint32_t)__shfl_xor((int)mb, 1, 64);
-    mb |= (uint32_t)__shfl_xor((int)mb, 2, 64);
-    if ((id & 3) == 0 && r < m)
-      reinterpret_cast<uint32_t *>(bits + (((int64_t)by * nbc + bq) * 64 + rr) * 4 + q)[(id >> 2) & 1] = mb;
+      for (int kk = 0; kk < 2; ++kk) {
+        const int64_t r = r0 + 32 * sl + row16 + 4 * rb, c = bx * 64 + 32 * kk + 8 * p;
+        v[sl][rb][kk] = u32x4{0u, 0u, 0u, 0u};
+        if (r < m && c < n) v[sl][rb][kk] = *reinterpret_cast<const u32x4 *>(Z + r * n + c);
+      }
+  // OR over the four lanes of a quad (DPP quad permutes 1, 0, 3, 2 and 2, 3, 0, 1)
+  auto quad_or = [](uint32_t x) {
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true);
+    return x | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true);
   };
+  auto pick = [&](const uint32_t (&w)[2][2]) { return p == 0 ? w[0][0] : p == 1 ? w[0][1] : p == 2 ? w[1][0] : w[1][1]; };
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int sl = 0; sl < 2; ++sl) {
+    uint32_t nib[2][2], mr[2][2], ml[2][2], plo[2][2], phi[2][2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int id = tid + 256 * i, rr = id >> 3, cc = (id & 7) * 8;
-      uint32_t lo = 0, hi = 0;
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        lo |= (quant_code(code_value(bf16_lo(v[q][i][e]), qz)) |
-               (quant_code(code_value(bf16_hi(v[q][i][e]), qz)) << 8)) << (16 * e);
-        hi |= (quant_code(code_value(bf16_lo(v[q][i][2 + e]), qz)) |
-               (quant_code(code_value(bf16_hi(v[q][i][2 + e]), qz)) << 8)) << (16 * e);
-      }
-      if constexpr (kTrans) {
-        // tile column pos holds M column slab_row(pos) of its 32-column slab:
-        // columns 8a + 4b + r (a = (cc % 32) / 8) sit at 16 b + 4 a + r, so the
-        // eight codes go out as two runs of four
-        uint8_t *row = &codes[q][rr][(cc & ~31) + 4 * ((cc >> 3) & 3)];
-        *reinterpret_cast<uint32_t *>(row) = lo;
-        *reinterpret_cast<uint32_t *>(row + 16) = hi;
-      }
-      if (kFwd && 4 * bq + q < gx) {
-        // K = columns: the eight codes are one operand dword, nibble i = column
-        // cc + i, stored straight from here.  Row rr of the tile is slab rr / 32,
-        // MFMA row m with slab_row(m) = rr % 32, i.e. lane 16 ((cc / 8) % 4) + m % 16
-        // and dword 2 (m / 16) + cc / 32.
-        const int s = rr & 31, mrow = 16 * ((s >> 2) & 1) + 4 * (s >> 3) + (s & 3);
-        const uint32_t w = (lo & 0xfu) | ((lo >> 4) & 0xf0u) | ((lo >> 8) & 0xf00u) | ((lo >> 12) & 0xf000u) |
-                           ((hi & 0xfu) << 16) | ((hi << 12) & 0xf00000u) | ((hi << 8) & 0xf000000u) |
-                           ((hi << 4) & 0xf0000000u);
-        frag[frag_dword_index(by * 2 + (rr >> 5), 4 * bq + q, KB, 16 * ((cc >> 3) & 3) + (mrow & 15),
-                              2 * (mrow >> 4) + (cc >> 5))] = w;
-      }
-      if constexpr (kMode == kQuantBwd) {
-        if (maskbits != nullptr) store_mask(q, i, maskbits, mask_mode);
-      } else if constexpr (kMode == kQuantSave) {
-        store_mask(q, i, maskbits, 0);
-        store_mask(q, i, maskbits2, 1);
-      }
-      if (kFwd && packed != nullptr) {
-        // 2-bit codes of these 8 columns (16 bits, least significant first);
-        // the even thread of each pair stores its neighbour's 16 bits with its
-        // own (4 bytes, 16 codes; n % 16 == 0 keeps them aligned, else 2-byte
-        // pieces)
-        const uint32_t b2 = (lo & 3u) | ((lo >> 6) & 0xcu) | ((lo >> 12) & 0x30u) | ((lo >> 18) & 0xc0u) |
-                            ((hi & 3u) << 8) | ((hi << 2) & 0xc00u) | ((hi >> 4) & 0x3000u) | ((hi >> 10) & 0xc000u);
-        const uint32_t nb = (uint32_t)__shfl_xor((int)b2, 1, 64);
-        const int64_t r = r0 + rr, c = (int64_t)(4 * bq + q) * 64 + cc;
-        if (r < m && c < n) {
-          uint8_t *dst = packed + r * (n / 4) + c / 4;
-          if ((n & 15) == 0) {
-            if ((id & 1) == 0) *reinterpret_cast<uint32_t *>(dst) = b2 | (nb << 16);
-          } else {
-            *reinterpret_cast<uint16_t *>(dst) = (uint16_t)b2;
+      for (int kk = 0; kk < 2; ++kk) {
+        const int rr = 32 * sl + row16 + 4 * rb;
+        const int64_t r = r0 + rr, c = bx * 64 + 32 * kk + 8 * p;
+        const bool in = r < m && c < n;  // n is a multiple of 8: the eight columns are in or out together
+        float z[8];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          z[2 * e] = code_value(bf16_lo(v[sl][rb][kk][e]), qz);
+          z[2 * e + 1] = code_value(bf16_hi(v[sl][rb][kk][e]), qz);
+        }
+        const uint32_t lo = quant_bytes(z[0], z[1], z[2], z[3]), hi = quant_bytes(z[4], z[5], z[6], z[7]);
+        nib[rb][kk] = bytes_to_nibbles(lo, hi);
+        if constexpr (kTrans) {
+          // tile column pos holds M column slab_row(pos) of its 32-column slab:
+          // columns 8a + 4b + e sit at 16 b + 4 a + e, so the eight codes go out as
+          // two runs of four
+          uint8_t *row = &codes[wave][rr][32 * kk + 4 * p];
+          *reinterpret_cast<uint32_t *>(row) = lo;
+          *reinterpret_cast<uint32_t *>(row + 16) = hi;
+        }
+        // masks: byte 4 kk + p of the row's 64-bit word, the quad's four bytes together
+        auto mask_word = [&](const MaskRange &range) {
+          uint32_t mb = 0;
+#pragma unroll
+          for (int e = 7; e >= 0; --e) mask_push(mb, z[e], range);
+          return quad_or(in ? mb << (8 * p) : 0u);
+        };
+        if constexpr (kMode == kQuantBwd) {
+          if (maskbits != nullptr) mr[rb][kk] = mask_word(mask_range(mask_mode));
+        } else if constexpr (kMode == kQuantSave) {
+          mr[rb][kk] = mask_word(mask_range(0));
+          ml[rb][kk] = mask_word(mask_range(1));
+        }
+        if (kFwd && packed != nullptr) {
+          // 2-bit codes: 16 bits per lane, 64 contiguous bits per quad
+          const uint32_t b2 = bytes_to_2bit(lo, hi);
+          if ((n & 31) == 0) {
+            const uint32_t w = b2 << (16 * (p & 1));
+            plo[rb][kk] = quad_or(p < 2 ? w : 0u);
+            phi[rb][kk] = quad_or(p < 2 ? 0u : w);
+          } else if (in) {
+            *reinterpret_cast<uint16_t *>(packed + r * (n / 4) + c / 4) = (uint16_t)b2;
           }
         }
       }
+    // K = columns: the lane's four words are its 16 bytes of the forward operand
+    if (kFwd && bx < gx)
+      *reinterpret_cast<u32x4 *>(frag + frag_dword_index(by * 2 + sl, (int)bx, KB, 16 * p + i16, 0)) =
+          u32x4{nib[0][0], nib[0][1], nib[1][0], nib[1][1]};
+    // lane p of a quad stores the word of row block p / 2, K half p % 2
+    const int rr = 32 * sl + row16 + 4 * (p >> 1);
+    if (r0 + rr < m) {
+      const int64_t at = ((((int64_t)by * nbc + bq) * 64 + rr) * 4 + wave) * 2 + (p & 1);
+      if constexpr (kMode == kQuantBwd) {
+        if (maskbits != nullptr) reinterpret_cast<uint32_t *>(maskbits)[at] = pick(mr);
+      } else if constexpr (kMode == kQuantSave) {
+        reinterpret_cast<uint32_t *>(maskbits)[at] = pick(mr);
+        reinterpret_cast<uint32_t *>(maskbits2)[at] = pick(ml);
+      }
+      if (kFwd && packed != nullptr && (n & 31) == 0) {
+        const int64_t c = bx * 64 + 32 * (p & 1);
+        if (c < n) *reinterpret_cast<u32x2 *>(packed + (r0 + rr) * (n / 4) + c / 4) = u32x2{pick(plo), pick(phi)};
+      }
     }
-  if constexpr (!kTrans) return;  // the operand dwords are stored above
+  }
+  if constexpr (!kTrans) return;  // the operand words are stored above
   // the transposed operand has KBt 64-row steps (rows padded to 128); the
   // forward's grid may hold further row tiles, which have nothing to store here
   if (by >= KBt) return;
@@ -228,25 +237,22 @@ __device__ __forceinline__ void quant_block(int bq, int by, int gx, const uint16
   // 16-lane group, source lane 2 k + h names row k of its eight rows, tile
   // positions 8 h .. 8 h + 7 of the 16-position half (16 mb ..) of the slab, and
   // output lane 8 h + c receives byte c of all eight rows, i.e. MFMA row
-  // 16 mb + 8 h + c, whose column the tile holds at that position.  Wave w
-  // writes dword w of every lane: lane L of group L / 16 reads rows
-  // 32 (w & 1) + 8 (L / 16) + 0..7.
-  const int lane = tid & 63, dw = tid >> 6, g16 = lane >> 4, j16 = lane & 15;
-  const int kloc = 32 * (dw & 1) + 8 * g16 + (j16 >> 1), ploc = 16 * (dw >> 1) + 8 * (j16 & 1);
+  // 16 mb + 8 h + c, whose column the tile holds at that position.  Lane L of
+  // group L / 16 reads rows 32 (dw % 2) + 8 (L / 16) + 0..7 for dword dw; a lane
+  // stores its four dwords together.
+  const int g16 = lane >> 4, j16 = lane & 15;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int bx = 4 * bq + q;
+  for (int slab = 0; slab < 2; ++slab) {
+    typedef int int2v __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) int2v lds_int2v;
+    u32x4 w;
 #pragma unroll
-    for (int slab = 0; slab < 2; ++slab) {
-      typedef int int2v __attribute__((ext_vector_type(2)));
-      typedef __attribute__((address_space(3))) int2v lds_int2v;
-      const int2v v = __builtin_amdgcn_ds_read_tr8_b64_v2i32(
-          (lds_int2v *)(&codes[q][kloc][slab * 32 + ploc]));
-      // eight bytes (codes 0..3) -> eight nibbles
-      const uint32_t x0 = (uint32_t)v[0] | ((uint32_t)v[0] >> 4), x1 = (uint32_t)v[1] | ((uint32_t)v[1] >> 4);
-      const uint32_t w = (x0 & 0xffu) | ((x0 >> 8) & 0xff00u) | ((x1 & 0xffu) << 16) | ((x1 << 8) & 0xff000000u);
-      frag_t[frag_dword_index(bx * 2 + slab, by, KBt, lane, dw)] = w;
+    for (int dw = 0; dw < 4; ++dw) {
+      const int kloc = 32 * (dw & 1) + 8 * g16 + (j16 >> 1), ploc = 16 * (dw >> 1) + 8 * (j16 & 1);
+      const int2v t = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_int2v *)(&codes[wave][kloc][slab * 32 + ploc]));
+      w[dw] = bytes_to_nibbles((uint32_t)t[0], (uint32_t)t[1]);
     }
+    *reinterpret_cast<u32x4 *>(frag_t + frag_dword_index((int)bx * 2 + slab, by, KBt, lane, 0)) = w;
   }
 }
 
@@ -437,7 +443,8 @@ __global__ __launch_bounds__(256) void k_pack2bit(const ST *__restrict__ src, in
       for (int h = 0; h < 2; ++h) {
         load8(src + w * 16 + 8 * h, v);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) bits |= quant_code(code_value(v[i], qz)) << (2 * (8 * h + i));
+        for (int i = 0; i < 8; ++i) v[i] = code_value(v[i], qz);
+        bits |= bytes_to_2bit(quant_bytes(v[0], v[1], v[2], v[3]), quant_bytes(v[4], v[5], v[6], v[7])) << (16 * h);
       }
     }
     *reinterpret_cast<uint32_t *>(packed + w * 4) = bits;
@@ -481,7 +488,7 @@ __global__ __launch_bounds__(256) void k_dequant(const ZT *__restrict__ src, int
     float z[D], c[D], y[D];
     loadD<D>(src + q * D, z);
 #pragma unroll
-    for (int k = 0; k < D; ++k) c[k] = (float)quant_code(z[k]);
+    for (int k = 0; k < D; ++k) c[k] = quant_code_f(z[k]);
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       float v = bb[j];
