@@ -434,6 +434,121 @@ __global__ __launch_bounds__(256, 1) void k_gemm_codes(
 // of each column block: whole groups, and 16 contiguous bytes of dZ.
 // ============================================================================
 
+// The epilogue of a block tile: columns c0 .. + 255, rows r0 .. + 16 NB - 1 of dZ; tm is
+// the tile's column block.
+template <bool kDge, int NB>
+__device__ __forceinline__ void dw_epilogue(floatx4 (&acc)[4][NB], int tm, int c0, int r0, int wave, int q, int c16,
+                                            const uint64_t *__restrict__ maskbits, int64_t nbc,
+                                            const uint16_t *__restrict__ Zb, const Quantizer &qz, int mask_mode,
+                                            const GradEst &est, int accumulate, void *__restrict__ dZ, int dz_bf16, int m,
+                                            int n) {
+  // ------------------------------------------------ gradient-estimator epilogue
+  // Lane L holds, for column block nb and slab mi, D[c .. c + 7, r] with
+  // r = r0 + 16 nb + L % 16 and c = c0 + 64 w + 32 mi + 8 (L / 16):
+  // acc[2 mi][nb] the first four, acc[2 mi + 1][nb] the last four.  dZ[r, c ..
+  // c + 7] = mask * D, the mask read from the bitmap the backward prepass wrote
+  // (one 64-bit word per row and wave: columns c0 + 64 w .. + 63; byte 4 mi +
+  // L / 16 holds these eight); with kDge, mask and slope come from Z[r, c ..
+  // c + 7] instead.  Rows r >= m fall outside the buffers; columns c >= n get
+  // an out-of-range offset.  Every load (mask words or Z, and old dZ when
+  // accumulating) of a column block is issued before the stores of the
+  // previous one: loads and stores share one counter.
+  // the bitmap tiles of rows r0 .. r0 + 255 (four 64-row bands of nbc tiles)
+  const __amdgpu_buffer_rsrc_t rmk = make_rsrc((const char *)maskbits + (int64_t)(r0 / 64) * nbc * 2048,
+                                               kDge ? 0 : ((int64_t)(m + 63) / 64 - r0 / 64) * nbc * 2048);
+  const __amdgpu_buffer_rsrc_t rz = make_rsrc(Zb + (int64_t)r0 * n, kDge ? (int64_t)(m - r0) * n * 2 : 0);
+  // this wave's 64 columns are word `wave` of each row of column block tm
+  const int es = dz_bf16 ? 2 : 4;
+  const __amdgpu_buffer_rsrc_t rg = make_rsrc((char *)dZ + (int64_t)r0 * n * es, (int64_t)(m - r0) * n * es);
+  u32x2 mk[2];        // mask word of the row, per buffer
+  u32x4 ov[2][2][2];  // old dZ per (buffer, mi, 16-byte half)
+  u32x4 zv[2][2];     // kDge: Z[r, c .. c + 7] per (buffer, mi)
+  auto eload = [&](int buf, int nb) {
+    const int rl = nb * 16 + c16;
+    if constexpr (kDge) {
+#pragma unroll
+      for (int mi = 0; mi < 2; ++mi) {
+        const int c = c0 + 64 * wave + 32 * mi + 8 * q;
+        zv[buf][mi] = __builtin_amdgcn_raw_buffer_load_b128(rz, c < n ? (uint32_t)(rl * n + c) * 2u : kOffNone, 0, 0);
+      }
+    } else {
+      mk[buf] = __builtin_amdgcn_raw_buffer_load_b64(
+          rmk, r0 + rl < m ? (int)((((rl >> 6) * nbc + tm) * 64 + (rl & 63)) * 32 + wave * 8) : (int)kOffNone, 0, 0);
+    }
+    if (!accumulate) return;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+      const int c = c0 + 64 * wave + 32 * mi + 8 * q;
+      const bool cv = c < n;
+      const uint32_t e = (uint32_t)(rl * n + c);
+      if (dz_bf16) {
+        ov[buf][mi][0] = __builtin_amdgcn_raw_buffer_load_b128(rg, cv ? e * 2u : kOffNone, 0, 0);
+      } else {
+        ov[buf][mi][0] = __builtin_amdgcn_raw_buffer_load_b128(rg, cv ? e * 4u : kOffNone, 0, 0);
+        ov[buf][mi][1] = __builtin_amdgcn_raw_buffer_load_b128(rg, cv ? e * 4u + 16u : kOffNone, 0, 0);
+      }
+    }
+  };
+  eload(0, 0);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int buf = nb & 1;
+    if (nb + 1 < NB) eload(buf ^ 1, nb + 1);
+    const int rl = nb * 16 + c16;
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+      const int c = c0 + 64 * wave + 32 * mi + 8 * q;
+      const bool cv = c < n;
+      const uint32_t e = (uint32_t)(rl * n + c);
+      float d8[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        d8[i] = acc[2 * mi][nb][i];
+        d8[4 + i] = acc[2 * mi + 1][nb][i];
+      }
+      // (times the quantiser scale: the chain rule through the code-domain value)
+      float g[8];
+      if constexpr (kDge) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t zw = zv[buf][mi][i >> 1];
+          const float z = code_value((i & 1) ? bf16_hi(zw) : bf16_lo(zw), qz);
+          g[i] = ste_pass(z, mask_mode) ? d8[i] * dge_slope(z, est) * qz.scale : 0.0f;
+        }
+      } else {
+        const uint32_t mb = mk[buf][mi] >> (8 * q);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) g[i] = ((mb >> i) & 1u) ? d8[i] * qz.scale : 0.0f;
+      }
+      if (dz_bf16) {
+        if (accumulate) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            g[2 * i] += bf16_lo(ov[buf][mi][0][i]);
+            g[2 * i + 1] += bf16_hi(ov[buf][mi][0][i]);
+          }
+        }
+        u32x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = pack_bf16x2(g[2 * i], g[2 * i + 1]);
+        __builtin_amdgcn_raw_buffer_store_b128(w, rg, cv ? e * 2u : kOffNone, 0, 0);
+      } else {
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          u32x4 w;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float v = g[4 * p + i];
+            if (accumulate) v += as_f(ov[buf][mi][p][i]);
+            w[i] = as_u(v);
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(w, rg, cv ? e * 4u + 16u * p : kOffNone, 0, 0);
+        }
+      }
+    }
+  }
+}
+
 template <bool kDge>
 __global__ __launch_bounds__(256, 1) void k_gemm_dw(const uint16_t *__restrict__ xt, const uint16_t *__restrict__ dyt,
                                                     int KBt, const uint64_t *__restrict__ maskbits, int64_t nbc,
@@ -575,96 +690,245 @@ __global__ __launch_bounds__(256, 1) void k_gemm_dw(const uint16_t *__restrict__
   LCVQ_WAIT_VM_LGKM0(0);
   mfma_drain();
 
-  // ------------------------------------------------ gradient-estimator epilogue
-  // Lane L holds, for column block nb and slab mi, D[c .. c + 7, r] with
-  // r = r0 + 16 nb + L % 16 and c = c0 + 64 w + 32 mi + 8 (L / 16):
-  // acc[2 mi][nb] the first four, acc[2 mi + 1][nb] the last four.  dZ[r, c ..
-  // c + 7] = mask * D, the mask read from the bitmap the backward prepass wrote
-  // (one 64-bit word per row and wave: columns c0 + 64 w .. + 63; byte 4 mi +
-  // L / 16 holds these eight); with kDge, mask and slope come from Z[r, c ..
-  // c + 7] instead.  Rows r >= m fall outside the buffers; columns c >= n get
-  // an out-of-range offset.  Every load (mask words or Z, and old dZ when
-  // accumulating) of a column block is issued before the stores of the
-  // previous one: loads and stores share one counter.
-  // the bitmap tiles of rows r0 .. r0 + 255 (four 64-row bands of nbc tiles)
-  const __amdgpu_buffer_rsrc_t rmk = make_rsrc((const char *)maskbits + (int64_t)(r0 / 64) * nbc * 2048,
-                                               kDge ? 0 : ((int64_t)(m + 63) / 64 - r0 / 64) * nbc * 2048);
-  const __amdgpu_buffer_rsrc_t rz = make_rsrc(Zb + (int64_t)r0 * n, kDge ? (int64_t)(m - r0) * n * 2 : 0);
-  // this wave's 64 columns are word `wave` of each row of column block tm
-  const int es = dz_bf16 ? 2 : 4;
-  const __amdgpu_buffer_rsrc_t rg = make_rsrc((char *)dZ + (int64_t)r0 * n * es, (int64_t)(m - r0) * n * es);
-  u32x2 mk[2];        // mask word of the row, per buffer
-  u32x4 ov[2][2][2];  // old dZ per (buffer, mi, 16-byte half)
-  u32x4 zv[2][2];     // kDge: Z[r, c .. c + 7] per (buffer, mi)
-  auto eload = [&](int buf, int nb) {
-    const int rl = nb * 16 + c16;
-    if constexpr (kDge) {
+  dw_epilogue<kDge, 16>(acc, tm, c0, r0, wave, q, c16, maskbits, nbc, Zb, qz, mask_mode, est, accumulate, dZ, dz_bf16, m,
+                        n);
+}
+
+// The same product on 256 x 128 tiles (wave w: in-features 64 w .. + 63, eight
+// out-feature blocks), two blocks per compute unit: one block's epilogue, which waits on
+// memory alone, runs under the other's products, and a partly empty last round costs
+// half as much.  A is loaded one step ahead instead of two (the other block fills the
+// wait); the rest of the order is k_gemm_dw's.
+template <bool kDge>
+__global__ __launch_bounds__(256, 2) void k_gemm_dw_half(const uint16_t *__restrict__ xt, const uint16_t *__restrict__ dyt,
+                                                         int KBt, const uint64_t *__restrict__ maskbits, int64_t nbc,
+                                                         const uint16_t *__restrict__ Zb, Quantizer qz, int mask_mode,
+                                                         GradEst est, int accumulate, void *__restrict__ dZ, int dz_bf16,
+                                                         int m, int n, int tiles_m, int tiles_n) {
+  constexpr int kStage = 16 * 1024;  // four 4 KiB B blocks
+  __shared__ __attribute__((aligned(1024))) char lds[4 * kStage];
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  tile_of_block(tiles_m, tiles_n, tm, tn);
+  const int c0 = tm * kTile, r0 = tn * (kTile / 2);
+  const __amdgpu_buffer_rsrc_t rsA =
+      make_rsrc(xt + (size_t)(tm * 8 + 2 * wave) * KBt * 2048, (int64_t)2 * KBt * 4096);
+  const __amdgpu_buffer_rsrc_t rsB = make_rsrc(dyt + (size_t)(tn * 4) * KBt * 2048, (int64_t)4 * KBt * 4096);
+
+  floatx4 acc[4][8];
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi) {
-        const int c = c0 + 64 * wave + 32 * mi + 8 * q;
-        zv[buf][mi] = __builtin_amdgcn_raw_buffer_load_b128(rz, c < n ? (uint32_t)(rl * n + c) * 2u : kOffNone, 0, 0);
-      }
-    } else {
-      mk[buf] = __builtin_amdgcn_raw_buffer_load_b64(
-          rmk, r0 + rl < m ? (int)((((rl >> 6) * nbc + tm) * 64 + (rl & 63)) * 32 + wave * 8) : (int)kOffNone, 0, 0);
-    }
-    if (!accumulate) return;
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
-      const int c = c0 + 64 * wave + 32 * mi + 8 * q;
-      const bool cv = c < n;
-      const uint32_t e = (uint32_t)(rl * n + c);
-      if (dz_bf16) {
-        ov[buf][mi][0] = __builtin_amdgcn_raw_buffer_load_b128(rg, cv ? e * 2u : kOffNone, 0, 0);
-      } else {
-        ov[buf][mi][0] = __builtin_amdgcn_raw_buffer_load_b128(rg, cv ? e * 4u : kOffNone, 0, 0);
-        ov[buf][mi][1] = __builtin_amdgcn_raw_buffer_load_b128(rg, cv ? e * 4u + 16u : kOffNone, 0, 0);
-      }
+    for (int j = 0; j < 8; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  acc_fence(acc);
+
+  auto issue = [&](int kb) {  // wave w copies block w of step kb: 4 direct-to-LDS loads
+#pragma unroll
+    for (int ph = 0; ph < 4; ++ph)
+      buffer_to_lds16(rsB, (lds_void *)(lds + (kb & 3) * kStage + (wave * 4 + ph) * 1024),
+                      (uint32_t)(((wave * KBt + kb) * 4 + ph) * 1024 + lane * 16));
+  };
+  u32x4 ca[2][2][2];  // [half-step][slab][16-row block]
+  auto load_a = [&](int kk2, int kb) {  // 4 loads per wave
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+      for (int fh = 0; fh < 2; ++fh)
+        ca[kk2][mi][fh] = __builtin_amdgcn_raw_buffer_load_b128(
+            rsA, (int)(((mi * KBt + kb) * 4 + 2 * fh + kk2) * 1024 + lane * 16), 0, 0);
+  };
+  bf16x8 b0[8], b1[8];
+  auto rd = [&](bf16x8 &dst, int kb, int nb, int kk2) {
+    dst = *reinterpret_cast<const bf16x8 *>(lds + (kb & 3) * kStage + ((nb >> 1) * 4 + 2 * (nb & 1) + kk2) * 1024 +
+                                            lane * 16);
+  };
+  auto half = [&](int kk2, bf16x8 (&b)[8], bf16x8 (&nxt)[8], int rkb, int rkk2) {
+#pragma unroll
+    for (int nb = 0; nb < 8; ++nb) {
+#pragma unroll
+      for (int mb = 0; mb < 4; ++mb) mfma16(acc[mb][nb], __builtin_bit_cast(bf16x8, ca[kk2][mb >> 1][mb & 1]), b[nb]);
+      rd(nxt[nb], rkb, nb, rkk2);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
-  eload(0, 0);
+  // The waits count loads in issue order.  Prologue: B 0, A 0 (8), B 1, B 2 (4 each): at
+  // most 8 in flight holds B 0 complete wherever the compiler leaves the A loads.  Before
+  // the barrier of step k: behind B k + 1 at most A of k - 1 and k, B k + 2, A (k, 1) and
+  // A (k + 1, 0), of which the last three (12 loads) may be in flight.
+  issue(0);
+  load_a(0, 0);
+  load_a(1, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  issue(1);
+  __builtin_amdgcn_sched_barrier(0);
+  issue(2);
+  __builtin_amdgcn_sched_barrier(0);
+  LCVQ_WAIT_VM_LGKM0(8);
+  LCVQ_BARRIER();
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int nb = 0; nb < 16; ++nb) {
-    const int buf = nb & 1;
-    if (nb + 1 < 16) eload(buf ^ 1, nb + 1);
-    const int rl = nb * 16 + c16;
+  for (int nb = 0; nb < 8; ++nb) rd(b0[nb], 0, nb, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int k = 0; k < KBt; ++k) {
+    half(0, b0, b1, k, 1);
+    load_a(0, k + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    LCVQ_WAIT_VM(12);
+    LCVQ_BARRIER();  // everyone's B k + 1 has landed, and everyone has read step k - 1
+    __builtin_amdgcn_sched_barrier(0);
+    issue(k + 3);
+    __builtin_amdgcn_sched_barrier(0);
+    half(1, b1, b0, k + 1, 0);
+    load_a(1, k + 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  LCVQ_WAIT_VM_LGKM0(0);
+  mfma_drain();
+  dw_epilogue<kDge, 8>(acc, tm, c0, r0, wave, q, c16, maskbits, nbc, Zb, qz, mask_mode, est, accumulate, dZ, dz_bf16, m, n);
+}
+
+// The same product where even those tiles leave compute units idle: 128 in-features x 64
+// out-features, the four waves splitting the tokens (wave w takes the 64-token steps w,
+// w + 4, ...; the steps are a multiple of four), each with an accumulator of the whole
+// tile.  Both operands come straight into registers, whole 1 KiB fragments, one step
+// ahead per half-step; the sums meet in LDS as in k_codes_split (lcvq_split.hip).
+// Bound: the loads' path into the compute unit, 24 KiB per 64 matrix instructions of a
+// wave (1.5 times those instructions' time), and latency.
+template <bool kDge>
+__global__ __launch_bounds__(256, 2) void k_gemm_dw_split(const uint16_t *__restrict__ xt, const uint16_t *__restrict__ dyt,
+                                                          int KBt, const uint64_t *__restrict__ maskbits, int64_t nbc,
+                                                          const uint16_t *__restrict__ Zb, Quantizer qz, int mask_mode,
+                                                          GradEst est, int accumulate, void *__restrict__ dZ, int dz_bf16,
+                                                          int m, int n, int tiles_m, int tiles_n) {
+  constexpr int MI = 4;
+  __shared__ floatx4 red[4][4][4][64];  // [source wave][column block][row block][lane], two slabs at a time
+  const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int tm, tn;
+  tile_of_block(tiles_m, tiles_n, tm, tn);
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(xt + (size_t)(tm * MI) * KBt * 2048, (int64_t)MI * KBt * 4096);
+  const __amdgpu_buffer_rsrc_t rsB = make_rsrc(dyt + (size_t)(tn * 2) * KBt * 2048, (int64_t)2 * KBt * 4096);
+
+  floatx4 acc[2 * MI][4];
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi) {
-      const int c = c0 + 64 * wave + 32 * mi + 8 * q;
-      const bool cv = c < n;
-      const uint32_t e = (uint32_t)(rl * n + c);
-      float d8[8];
+  for (int i = 0; i < 2 * MI; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        d8[i] = acc[2 * mi][nb][i];
-        d8[4 + i] = acc[2 * mi + 1][nb][i];
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  acc_fence(acc);
+  u32x4 ca[2][2 * MI], cb[2][4];  // [half-step]
+  auto load = [&](int kk2, int kb) {  // (past the last step: other slabs' data or zeros, never used)
+#pragma unroll
+    for (int p = 0; p < 2 * MI; ++p)
+      ca[kk2][p] = __builtin_amdgcn_raw_buffer_load_b128(
+          rsA, (int)((((p >> 1) * KBt + kb) * 4 + 2 * (p & 1) + kk2) * 1024 + lane * 16), 0, 0);
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+      cb[kk2][nb] = __builtin_amdgcn_raw_buffer_load_b128(
+          rsB, (int)((((nb >> 1) * KBt + kb) * 4 + 2 * (nb & 1) + kk2) * 1024 + lane * 16), 0, 0);
+  };
+  load(0, wave);
+  __builtin_amdgcn_sched_barrier(0);
+  load(1, wave);
+  __builtin_amdgcn_sched_barrier(0);
+  for (int kb = wave; kb < KBt; kb += 4) {
+#pragma unroll
+    for (int kk2 = 0; kk2 < 2; ++kk2) {
+#pragma unroll
+      for (int p = 0; p < 2 * MI; ++p)
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+          mfma16(acc[p][nb], __builtin_bit_cast(bf16x8, ca[kk2][p]), __builtin_bit_cast(bf16x8, cb[kk2][nb]));
+      __builtin_amdgcn_sched_barrier(0);
+      load(kk2, kb + 4);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  mfma_drain();
+
+  // ---- wave w finishes out-features 16 w .. + 15: lane L in-features 32 mi + 8 (L / 16)
+  // .. + 7 of row r = 64 tn + 16 w + L % 16
+  const int64_t r = (int64_t)tn * 64 + 16 * wave + c16;
+  const int cb0 = tm * 32 * MI + 8 * q, es = dz_bf16 ? 2 : 4;
+  const int64_t rt = (int64_t)tn * 64;
+  const __amdgpu_buffer_rsrc_t rmk = make_rsrc((const char *)maskbits + (int64_t)tn * nbc * 2048, kDge ? 0 : nbc * 2048);
+  const __amdgpu_buffer_rsrc_t rz = make_rsrc(Zb + rt * n, kDge ? (int64_t)(m - rt) * n * 2 : 0);
+  const __amdgpu_buffer_rsrc_t rg = make_rsrc((char *)dZ + rt * n * es, (int64_t)(m - rt) * n * es);
+  const int rl = 16 * wave + c16;
+  u32x4 zv[kDge ? MI : 1];
+  uint32_t mk[kDge ? 1 : MI];
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    const int c = cb0 + 32 * mi;
+    if constexpr (kDge) {
+      zv[mi] = __builtin_amdgcn_raw_buffer_load_b128(rz, c < n ? (uint32_t)(rl * n + c) * 2u : kOffNone, 0, 0);
+    } else {  // the 32-bit half of the row's word: bitmap tile c / 256, word (c / 64) % 4
+      const int c0 = tm * 32 * MI + 32 * mi;
+      mk[mi] = __builtin_amdgcn_raw_buffer_load_b32(
+          rmk, r < m ? (int)(((c0 >> 8) * 64 + rl) * 32 + ((c0 >> 6) & 3) * 8 + ((c0 >> 5) & 1) * 4) : (int)kOffNone, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int ph = 0; ph < MI / 2; ++ph) {
+    u32x4 ov[2][2];
+    if (accumulate) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = cb0 + 32 * (2 * ph + h);
+        const uint32_t e = (uint32_t)(rl * n + c);
+        ov[h][0] = __builtin_amdgcn_raw_buffer_load_b128(rg, c < n ? e * es : kOffNone, 0, 0);
+        if (!dz_bf16) ov[h][1] = __builtin_amdgcn_raw_buffer_load_b128(rg, c < n ? e * 4u + 16u : kOffNone, 0, 0);
       }
-      // (times the quantiser scale: the chain rule through the code-domain value)
-      float g[8];
-      if constexpr (kDge) {
+    }
+    if (ph > 0) __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint32_t zw = zv[buf][mi][i >> 1];
-          const float z = code_value((i & 1) ? bf16_hi(zw) : bf16_lo(zw), qz);
-          g[i] = ste_pass(z, mask_mode) ? d8[i] * dge_slope(z, est) * qz.scale : 0.0f;
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        floatx4 t;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float x;
+          asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(acc[4 * ph + k][nb][e]));
+          t[e] = x;
         }
-      } else {
-        const uint32_t mb = mk[buf][mi] >> (8 * q);
+        red[wave][nb][k][lane] = t;
+      }
+    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) g[i] = ((mb >> i) & 1u) ? d8[i] * qz.scale : 0.0f;
+    for (int h = 0; h < 2; ++h) {
+      const int mi = 2 * ph + h, c = cb0 + 32 * mi;
+      const uint32_t e0 = (uint32_t)(rl * n + c);
+      float g[8];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        floatx4 v = red[0][wave][2 * h + k][lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) v += red[w][wave][2 * h + k][lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[4 * k + e] = v[e];
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if constexpr (kDge) {
+          const float z = code_value((i & 1) ? bf16_hi(zv[mi][i >> 1]) : bf16_lo(zv[mi][i >> 1]), qz);
+          g[i] = ste_pass(z, mask_mode) ? g[i] * dge_slope(z, est) * qz.scale : 0.0f;
+        } else {
+          g[i] = ((mk[mi] >> (8 * q + i)) & 1u) ? g[i] * qz.scale : 0.0f;
+        }
       }
       if (dz_bf16) {
         if (accumulate) {
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            g[2 * i] += bf16_lo(ov[buf][mi][0][i]);
-            g[2 * i + 1] += bf16_hi(ov[buf][mi][0][i]);
+            g[2 * i] += bf16_lo(ov[h][0][i]);
+            g[2 * i + 1] += bf16_hi(ov[h][0][i]);
           }
         }
         u32x4 w;
 #pragma unroll
         for (int i = 0; i < 4; ++i) w[i] = pack_bf16x2(g[2 * i], g[2 * i + 1]);
-        __builtin_amdgcn_raw_buffer_store_b128(w, rg, cv ? e * 2u : kOffNone, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(w, rg, c < n ? e0 * 2u : kOffNone, 0, 0);
       } else {
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
@@ -672,10 +936,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm_dw(const uint16_t *__restrict__
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             float v = g[4 * p + i];
-            if (accumulate) v += as_f(ov[buf][mi][p][i]);
-            w[i] = as_u(v);
+            if (accumulate) v += __uint_as_float(ov[h][p][i]);
+            w[i] = __float_as_uint(v);
           }
-          __builtin_amdgcn_raw_buffer_store_b128(w, rg, cv ? e * 4u + 16u * p : kOffNone, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(w, rg, c < n ? e0 * 4u + 16u * p : kOffNone, 0, 0);
         }
       }
     }
@@ -747,19 +1011,38 @@ hipError_t launch_map_combine(const float *mapp, int rows, int d, int accumulate
   return hipGetLastError();
 }
 
+// Which weight-gradient tile: the time of the busiest compute unit, from the measured
+// time (ns) of a block per 64-token step plus its epilogue: 256 x 256, one block per
+// unit; 256 x 128, two blocks side by side or one alone; 128 x 64 with the tokens split
+// over the waves, two or one.  At 4096^3 100, 106 and 137 us; 512 tokens of 28672 x 8192
+// 332, 290 and 466 (the epilogue counts); 4096 tokens of 2048 x 2048 82, 64 and 42, 16384
+// of 1024 x 2048 295, 230 and 76 (few tiles).
+enum DwTile { kDwFull, kDwHalf, kDwSplit };
+static DwTile dw_tile(int64_t m, int64_t n, int64_t KBt) {
+  const int64_t cols = ceil_div(n, 256);
+  auto load = [](int64_t blocks) { return ceil_div(blocks, 256); };  // blocks on the busiest unit
+  auto cost = [&](int64_t b, int64_t pair_step, int64_t pair, int64_t one_step, int64_t one, int64_t steps) {
+    return b / 2 * (pair_step * steps + pair) + (b & 1) * (one_step * steps + one);
+  };
+  const int64_t full = load(cols * ceil_div(m, 256)) * (1450 * KBt + 10000);
+  const int64_t half = cost(load(cols * ceil_div(m, 128)), 1550, 6000, 920, 4000, KBt);
+  const int64_t split = cost(load(ceil_div(n, 128) * ceil_div(m, 64)), 2300, 4000, 1150, 3000, KBt / 4);
+  return full <= half && full <= split ? kDwFull : half <= split ? kDwHalf : kDwSplit;
+}
+
 hipError_t launch_dw_bf16(const uint16_t *xt, const uint16_t *dyt, const uint64_t *maskbits, const uint16_t *Z,
                           const Quantizer &qz, int mask_mode, const GradEst &est, int accumulate, void *dZ,
                           bool dz_bf16, int64_t N, int64_t m, int64_t n, hipStream_t st) {
-  const int tiles_m = (int)ceil_div(n, kTile), tiles_n = (int)ceil_div(m, kTile);
-  const int KBt = (int)(bwd_tokens(N) / 64);  // even
-  if (est.dge)
-    k_gemm_dw<true><<<tiles_m * tiles_n, 256, 0, st>>>(xt, dyt, KBt, nullptr, mask_col_blocks(n), Z, qz,
-                                                       mask_mode, est, accumulate, dZ, dz_bf16 ? 1 : 0, (int)m, (int)n, tiles_m,
-                                                       tiles_n);
-  else
-    k_gemm_dw<false><<<tiles_m * tiles_n, 256, 0, st>>>(xt, dyt, KBt, maskbits, mask_col_blocks(n), nullptr,
-                                                        qz, mask_mode, est, accumulate, dZ, dz_bf16 ? 1 : 0, (int)m,
-                                                        (int)n, tiles_m, tiles_n);
+  const int KBt = (int)(bwd_tokens(N) / 64);  // a multiple of four
+  const DwTile t = dw_tile(m, n, KBt);
+  const int tiles_m = (int)ceil_div(n, t == kDwSplit ? 128 : 256);
+  const int tiles_n = (int)ceil_div(m, t == kDwSplit ? 64 : t == kDwHalf ? 128 : 256);
+  auto k = t == kDwSplit  ? (est.dge ? k_gemm_dw_split<true> : k_gemm_dw_split<false>)
+           : t == kDwHalf ? (est.dge ? k_gemm_dw_half<true> : k_gemm_dw_half<false>)
+                          : (est.dge ? k_gemm_dw<true> : k_gemm_dw<false>);
+  k<<<tiles_m * tiles_n, 256, 0, st>>>(xt, dyt, KBt, est.dge ? nullptr : maskbits, mask_col_blocks(n), est.dge ? Z : nullptr,
+                                       qz, mask_mode, est, accumulate, dZ, dz_bf16 ? 1 : 0, (int)m, (int)n, tiles_m,
+                                       tiles_n);
   return hipGetLastError();
 }
 }  // namespace lcvq
