@@ -110,64 +110,60 @@ __global__ __launch_bounds__(256, 2) void k_codes_split(
     // dY rows.  Lanes that follow each other must read memory that follows each
     // other: with the operand's own mapping (neighbouring lanes = tokens, a row
     // apart) a 1 KiB load takes the address path 64 cycles instead of 16
-    // (measured 8.5 against 23 TB/s from the L2).  So lane L loads chunk L % 8 (16
-    // bytes) of row 8 r + L / 8, whole 128-byte lines, and the wave's own LDS
-    // stage turns that into operands: row t's chunk k at 128 t + 16 (k ^ (t % 8)),
-    // which keeps both the writes and the reads free of bank conflicts.  Only the
-    // wave itself uses its stages, so no barrier is needed.
-    constexpr int kG = MI == 4 ? 1 : 2;  // steps of dY in registers (MI = 4: two would leave no room for a second block)
-    u32x4 g[kG][8], b0[4], b1[4];
+    // (measured 8.5 against 23 TB/s from the L2).  So a direct-to-LDS load brings
+    // eight whole 128-byte runs, lane L chunk (L % 8) ^ (L / 8) (16 bytes) of row
+    // 8 r + L / 8, into the wave's own LDS stage: row t's chunk k sits at
+    // 128 t + 16 (k ^ (t % 8)), which keeps the operand reads free of bank
+    // conflicts.  Chunks outside dY arrive as zeros.  Only the wave itself uses its
+    // two stages, so no barrier is needed.  (Through registers and LDS writes the
+    // same product took 17.4 us instead of 15.7 at 256 tokens of 4096 x 4096, 82
+    // instead of 79 at 1000 of 11008 x 4096.)
+    u32x4 b0[4], b1[4];
     char *stage = lds + wave * 16384;
-    const int lrow = lane >> 3, lch = lane & 7;
+    const int lrow = lane >> 3, lch = (lane & 7) ^ lrow;
     const uint32_t goff = (uint32_t)((lrow * ldB + 8 * lch) * 2);
-    const uint32_t woff = (uint32_t)(lrow * 128 + ((lch ^ lrow) << 4));
     const uint32_t roff = (uint32_t)(c16 * 128 + ((q ^ (c16 & 7)) << 4));
     const int kb_lim = (int)ldB - 8 - 8 * lch;  // the lane's chunk exists at step kb iff 64 kb <= kb_lim
     const uint32_t gstep = (uint32_t)(16 * ldB);  // eight rows
-    auto load_g = [&](u32x4 (&v)[8], int kb) {
+    auto load_g = [&](int st, int kb) {
       const uint32_t off = kb < KB && kb * 64 <= kb_lim ? goff + (uint32_t)kb * 128u : kOffNone;
 #pragma unroll
       for (int r = 0; r < 8; ++r)
-        v[r] = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(off == kOffNone ? kOffNone : off + r * gstep), 0, 0);
-    };
-    auto put = [&](const u32x4 (&v)[8], int st) {
-#pragma unroll
-      for (int r = 0; r < 8; ++r) *reinterpret_cast<u32x4 *>(stage + st * 8192 + r * 1024 + woff) = v[r];
+        buffer_to_lds16(rsB, (lds_void *)(stage + st * 8192 + r * 1024), off == kOffNone ? kOffNone : off + r * gstep);
     };
     auto get = [&](u32x4 (&b)[4], int st, int kk2) {
 #pragma unroll
       for (int tb = 0; tb < 4; ++tb)
         b[tb] = *reinterpret_cast<const u32x4 *>(stage + st * 8192 + tb * 2048 + (roff ^ (kk2 << 6)));
     };
+    // The wait before a stage is read leaves the codes loads that were issued after
+    // it in flight.
     load_a(0, wave);
-    load_g(g[0], wave);
+    load_g(0, wave);
     __builtin_amdgcn_sched_barrier(0);
     load_a(1, wave + kW);
-    if constexpr (kG == 2) load_g(g[1], wave + kW);
-    __builtin_amdgcn_sched_barrier(0);
-    put(g[0], 0);
-    load_g(g[0], wave + kG * kW);
-    get(b0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     for (int kb = wave; kb < KB; kb += 2 * kW) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         bf16x8 an;
         const int k = kb + kW * u;
+        LCVQ_WAIT_VM(MI);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        get(b0, u, 0);
         get(b1, u, 1);
         __builtin_amdgcn_sched_barrier(0);
+        load_g(u ^ 1, k + kW);
+        __builtin_amdgcn_sched_barrier(0);
         half(u, 0, an, b0);
-        __builtin_amdgcn_sched_barrier(0);
-        put(g[(u + 1) % kG], u ^ 1);
-        load_g(g[(u + 1) % kG], k + (1 + kG) * kW);
-        __builtin_amdgcn_sched_barrier(0);
         half(u, 1, an, b1);
         __builtin_amdgcn_sched_barrier(0);
-        get(b0, u ^ 1, 0);
         load_a(u, k + 2 * kW);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+    LCVQ_WAIT_ALL();  // the last stage's loads have landed before the sums overwrite it
     __syncthreads();  // the stages become the waves' sums
   }
   mfma_drain();
