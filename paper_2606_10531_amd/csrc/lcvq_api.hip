@@ -94,9 +94,10 @@ BwdLayout bwd_layout(int64_t N, int64_t m, int64_t n, bool bf16) {
     L.dyt = L.xt + up256((size_t)lcvq::round_up(n, 256) * Nt * 2);
     // straight-through mask of Z, one bit per element (rows of whole 64-bit words)
     L.mask = L.dyt + up256((size_t)lcvq::round_up(m, 256) * Nt * 2);
-    // the map gradients' per-block partial sums (d d + d <= 72 entries)
+    // the map gradients' per-block partial sums (d d + d <= 72 entries), for the most
+    // blocks of any tile: a workspace serves every smaller N
     L.map = L.mask + up256((size_t)lcvq::mask_bytes(m, n));
-    L.total = L.map + up256((size_t)lcvq::map_rows(N, n) * 72 * 4);
+    L.total = L.map + up256((size_t)lcvq::map_rows_max(N, n) * 72 * 4);
   } else {
     // the map gradients' per-block partial sums alone
     L.total = up256((size_t)lcvq::map_rows_f32(m, n) * 72 * 4);
@@ -716,7 +717,7 @@ static lcvq_status_t linear_bwd(int64_t N, int64_t m, int64_t n, int32_t d, int3
     }
     if (want_map) {
       Timed tm(LCVQ_K_MAP_SUM, st);
-      e = tm.done(lcvq::launch_map_combine(mapp, lcvq::map_rows(N, n), d, accumulate, dA, db, st));
+      e = tm.done(lcvq::launch_map_combine(mapp, lcvq::map_rows(N, m, n), d, accumulate, dA, db, st));
       if (e != hipSuccess) return hip_fail(e, "map-gradient sum launch");
     }
     return ok();

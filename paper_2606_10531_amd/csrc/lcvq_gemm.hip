@@ -950,8 +950,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dw_split(const uint16_t *__rest
 
 hipError_t launch_fwd_bf16(const uint32_t *frag, const uint16_t *Xp, int64_t ldp, const float *s,
                            uint16_t *Y, int64_t N, int64_t m, int64_t n, hipStream_t st) {
-  (void)n;
-  if (const int slabs = fwd_slabs(N, m)) return launch_fwd_split(slabs, frag, Xp, ldp, s, Y, N, m, st);
+  if (const int slabs = fwd_slabs(N, m, n)) return launch_fwd_split(slabs, frag, Xp, ldp, s, Y, N, m, st);
   const int tiles_m = (int)ceil_div(m, 2 * kTile), tiles_n = (int)ceil_div(N, kTile / 2);  // 512 x 128 tiles
   const int KB = (int)(ldp / kKStep);  // even: ldp is a multiple of 128
   const int64_t Np = round_up(N, kTile);  // row stride of the partial sums of s
@@ -963,7 +962,7 @@ hipError_t launch_fwd_bf16(const uint32_t *frag, const uint16_t *Xp, int64_t ldp
 hipError_t launch_dx_bf16(const uint32_t *frag, const uint16_t *dY, const float *rsp, const float *A, const float *b,
                           int d, uint16_t *dX, const uint16_t *X, float *mapp, int64_t N, int64_t m, int64_t n,
                           hipStream_t st) {
-  if (const int slabs = dx_slabs(N, n)) return launch_dx_split(slabs, frag, dY, rsp, A, b, d, dX, X, mapp, N, m, n, st);
+  if (const int slabs = dx_slabs(N, m, n)) return launch_dx_split(slabs, frag, dY, rsp, A, b, d, dX, X, mapp, N, m, n, st);
   const int parts = rowsum_parts(m);
   const int64_t Nt = bwd_tokens(N);  // row stride of the partial row sums
   const int tiles_m = (int)ceil_div(n, kTile), tiles_n = (int)ceil_div(N, kTile);
@@ -978,8 +977,8 @@ hipError_t launch_dx_bf16(const uint32_t *frag, const uint16_t *dY, const float 
   return hipGetLastError();
 }
 
-int map_rows(int64_t N, int64_t n) {
-  const int slabs = dx_slabs(N, n);
+int map_rows(int64_t N, int64_t m, int64_t n) {
+  const int slabs = dx_slabs(N, m, n);
   return (int)(slabs ? ceil_div(n, 32 * slabs) * ceil_div(N, 64) : ceil_div(n, kTile) * ceil_div(N, kTile));
 }
 
@@ -1011,22 +1010,28 @@ hipError_t launch_map_combine(const float *mapp, int rows, int d, int accumulate
   return hipGetLastError();
 }
 
-// Which weight-gradient tile: the time of the busiest compute unit, from the measured
-// time (ns) of a block per 64-token step plus its epilogue: 256 x 256, one block per
-// unit; 256 x 128, two blocks side by side or one alone; 128 x 64 with the tokens split
-// over the waves, two or one.  At 4096^3 100, 106 and 137 us; 512 tokens of 28672 x 8192
-// 332, 290 and 466 (the epilogue counts); 4096 tokens of 2048 x 2048 82, 64 and 42, 16384
-// of 1024 x 2048 295, 230 and 76 (few tiles).
+// Which weight-gradient tile: the time of the busiest compute unit, ns per 64-token step
+// and per block, plus a part per block for the chip filling up, fitted to 107 shapes of
+// 64 .. 16384 tokens and 512 .. 28672 features (which it gives to 4 .. 9 %): 256 x 256, one
+// block per unit; 256 x 128, two blocks side by side or one alone; 128 x 64 with the
+// tokens split over the waves (steps of 256 tokens), two or one.  Measured (us, full /
+// half / split): 4096^3 100 / 106 / 137; 512 tokens of 28672 x 8192 332 / 290 / 466 (the
+// epilogue counts); 4096 of 2048 x 2048 82 / 64 / 42 and 16384 of 1024 x 2048 295 / 230 / 76
+// (few tiles); 12130 of 16296 x 592 240 / 309 / 337; 5322 of 784 x 10408 111 / 128 / 129.
 enum DwTile { kDwFull, kDwHalf, kDwSplit };
 static DwTile dw_tile(int64_t m, int64_t n, int64_t KBt) {
-  const int64_t cols = ceil_div(n, 256);
-  auto load = [](int64_t blocks) { return ceil_div(blocks, 256); };  // blocks on the busiest unit
-  auto cost = [&](int64_t b, int64_t pair_step, int64_t pair, int64_t one_step, int64_t one, int64_t steps) {
-    return b / 2 * (pair_step * steps + pair) + (b & 1) * (one_step * steps + one);
+  struct Cost {  // ns: two blocks (per step, each), one block, per 256 blocks, in all
+    int64_t pair_step, pair, one_step, one, full_step, full, base;
   };
-  const int64_t full = load(cols * ceil_div(m, 256)) * (1450 * KBt + 10000);
-  const int64_t half = cost(load(cols * ceil_div(m, 128)), 1550, 6000, 920, 4000, KBt);
-  const int64_t split = cost(load(ceil_div(n, 128) * ceil_div(m, 64)), 2300, 4000, 1150, 3000, KBt / 4);
+  auto cost = [](const Cost &c, int64_t blocks, int64_t steps) {
+    const int64_t b = ceil_div(blocks, 256);  // on the busiest unit
+    return b / 2 * (c.pair_step * steps + c.pair) + b % 2 * (c.one_step * steps + c.one) +
+           blocks * (c.full_step * steps + c.full) / 256 + c.base;
+  };
+  const int64_t cols = ceil_div(n, 256);
+  const int64_t full = cost({2100, 15200, 1050, 7600, 310, 2500, 3200}, cols * ceil_div(m, 256), KBt),
+                half = cost({1130, 4300, 810, 3800, 210, 1100, 2600}, cols * ceil_div(m, 128), KBt),
+                split = cost({1030, 2800, 670, 1800, 580, 300, 4600}, ceil_div(n, 128) * ceil_div(m, 64), KBt / 4);
   return full <= half && full <= split ? kDwFull : half <= split ? kDwHalf : kDwSplit;
 }
 

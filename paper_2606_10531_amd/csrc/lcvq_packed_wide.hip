@@ -284,7 +284,7 @@ hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int
 hipError_t launch_packed_wide(const PackedWidePlan &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc,
                               void *Y, bool y_bf16, hipStream_t st) {
   // 128 or 64 rows per tile: rounds of tiles over the compute units times a tile's
-  // time (per 64 K, ns: the values of codes_split_slabs)
+  // time per 64 K (ns, measured with the chip full)
   const int64_t tt = ceil_div(Nc, 64), t4 = ceil_div(m, 128) * tt, t2 = ceil_div(m, 64) * tt;
   const bool four = 187 * ceil_div(t4, 256) <= 117 * ceil_div(t2, 256);
   const int tiles_m = (int)ceil_div(m, four ? 128 : 64);

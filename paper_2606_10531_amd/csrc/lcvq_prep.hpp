@@ -123,12 +123,14 @@ hipError_t launch_adamw(float *theta, const void *grad, bool grad_bf16, float *m
 // bf16 matrix-core products (lcvq_gemm.hip)
 hipError_t launch_fwd_bf16(const uint32_t *frag, const uint16_t *Xp, int64_t ldp, const float *s,
                            uint16_t *Y, int64_t N, int64_t m, int64_t n, hipStream_t st);
-// Map gradients of the input-gradient product: each of its map_rows(N, n)
-// blocks (of the tiles that dx_slabs picks) stores its partial sums of dA (d x d) and db (d), entry-major (entry
-// e of block b at mapp[e * map_rows + b]; every place is written, so mapp
-// needs no clearing); launch_map_combine then sums each entry over the blocks
-// in a fixed order into dA and db (added to them when accumulating).
-int map_rows(int64_t N, int64_t n);
+// Map gradients of the input-gradient product: each of its map_rows(N, m, n) blocks
+// (of the tiles that dx_slabs picks) stores its partial sums of dA (d x d) and db (d),
+// entry-major (entry e of block b at mapp[e * map_rows + b]; every place is written, so
+// mapp needs no clearing); launch_map_combine then sums each entry over the blocks in a
+// fixed order into dA and db (added to them when accumulating).  map_rows_max: the most
+// blocks that any tile gives, which grows with N and n where map_rows need not.
+int map_rows(int64_t N, int64_t m, int64_t n);
+inline int map_rows_max(int64_t N, int64_t n) { return (int)(ceil_div(n, 64) * ceil_div(N, 64)); }
 hipError_t launch_dx_bf16(const uint32_t *frag, const uint16_t *dY, const float *rsp, const float *A, const float *b,
                           int d, uint16_t *dX, const uint16_t *X, float *mapp, int64_t N, int64_t m, int64_t n,
                           hipStream_t st);
@@ -137,9 +139,9 @@ hipError_t launch_map_combine(const float *mapp, int rows, int d, int accumulate
 // The same two products on tiles of 32 slabs rows x 64 tokens whose waves split K
 // (lcvq_split.hip), slabs 2 or 4; codes_split_slabs says when (0: the wide tiles of
 // lcvq_gemm.hip).
-int codes_split_slabs(int64_t rows, int64_t tokens, bool dx);
-inline int fwd_slabs(int64_t N, int64_t m) { return codes_split_slabs(m, N, false); }
-inline int dx_slabs(int64_t N, int64_t n) { return codes_split_slabs(n, N, true); }
+int codes_split_slabs(int64_t rows, int64_t tokens, int64_t K, bool dx);
+inline int fwd_slabs(int64_t N, int64_t m, int64_t n) { return codes_split_slabs(m, N, n, false); }
+inline int dx_slabs(int64_t N, int64_t m, int64_t n) { return codes_split_slabs(n, N, m, true); }
 hipError_t launch_fwd_split(int slabs, const uint32_t *frag, const uint16_t *Xp, int64_t ldp, const float *s, uint16_t *Y,
                             int64_t N, int64_t m, hipStream_t st);
 hipError_t launch_dx_split(int slabs, const uint32_t *frag, const uint16_t *dY, const float *rsp, const float *A,

@@ -344,24 +344,32 @@ __global__ __launch_bounds__(256, 2) void k_codes_split(
 }
 
 // ---- the choice of tiles -----------------------------------------------------
-// Rounds of tiles over the 256 compute units times what a tile takes per 64-wide
-// step, measured with the chip full (ns; forward 512 x 128 wide tile, then 128 and
-// 64 rows x 64 tokens; input gradient 256 x 256 wide tile, then the same).  A full
-// wide tile costs less per output (forward 7 %, input gradient a third), so the
-// small tiles win where the wide ones leave a round partly empty: at 256 tokens and
-// 4096 x 4096, 16 wide tiles take 80 (forward) and 90 us (input gradient), 256 of
-// the smallest 12 and 17; at 1000 tokens and 11008 x 4096 the input gradient 217
-// against 82; the forward of 4096 x 11008 at 2048 tokens 213 against 128.  At 4096^3
-// every tile of one wide round is busy and stays ahead (98 against 101, 108 against
-// 129).
-int codes_split_slabs(int64_t rows, int64_t tokens, bool dx) {
-  constexpr int64_t kNs[2][3] = {{1400, 187, 117}, {1500, 240, 155}};
-  const int64_t *ns = kNs[dx ? 1 : 0];
-  auto rounds = [](int64_t tiles) { return ceil_div(tiles, 256); };
-  const int64_t wide = dx ? ceil_div(rows, 256) * ceil_div(tokens, 256) : ceil_div(rows, 512) * ceil_div(tokens, 128);
+// A product's time by tile: per round of tiles over the 256 compute units a fixed part
+// (filling the pipeline, the epilogue) and a part per 64-wide step, plus a part per tile
+// and step (the chip filling up: power, operand traffic), fitted to both products of
+// 107 shapes of 64 .. 16384 tokens and 512 .. 28672 features, which it gives to 3 % for
+// the wide tile (512 x 128; input gradient 256 x 256) and 5 .. 10 % for the small ones.
+// Rows of dY that don't begin on 128-byte lines cost the small input-gradient tile,
+// which reads them in 128-byte runs, up to a fifth.  Measured (us, wide / 128 rows /
+// 64 rows): forward, 256 tokens of 4096 x 4096 80 / - / 12; 2048 of 4096 x 11008
+// 213 / 128 / -; 4228 of 23936 x 1128 196 / 228 / 292; 5262 of 6280 x 10136 596 / 471 /
+// 586.  Input gradient, 1000 of 11008 x 4096 217 / 79 / -; 958 of 26032 x 3176 483 / 169 /
+// 219; 2404 of 22736 x 10056 894 / 993 / 1473; 4096^3 108 / 129 / -.
+int codes_split_slabs(int64_t rows, int64_t tokens, int64_t K, bool dx) {
+  struct Cost {  // ns: per round and step, per round, per 256 tiles and step, in all
+    int64_t step, round, full, base;
+  };
+  constexpr Cost kCost[2][3] = {{{1080, 6400, 140, 2000}, {153, 1500, 12, 4900}, {92, 840, 21, 4000}},
+                                {{1110, 17000, 175, 400}, {167, 3100, 12, 6000}, {124, 2100, 0, 5300}}};
+  const int64_t KB = round_up(K, 128) / 64;
+  auto cost = [&](int i, int64_t tiles) {
+    const Cost &c = kCost[dx ? 1 : 0][i];
+    const int64_t full = c.full + (dx && i > 0 && K % 64 != 0 ? 40 : 0);
+    return ceil_div(tiles, 256) * (c.step * KB + c.round) + tiles * full * KB / 256 + c.base;
+  };
   const int64_t tt = ceil_div(tokens, 64);
-  const int64_t c0 = ns[0] * rounds(wide), c4 = ns[1] * rounds(ceil_div(rows, 128) * tt),
-                c2 = ns[2] * rounds(ceil_div(rows, 64) * tt);
+  const int64_t c0 = cost(0, dx ? ceil_div(rows, 256) * ceil_div(tokens, 256) : ceil_div(rows, 512) * ceil_div(tokens, 128)),
+                c4 = cost(1, ceil_div(rows, 128) * tt), c2 = cost(2, ceil_div(rows, 64) * tt);
   if (c0 <= c4 && c0 <= c2) return 0;
   return c2 < c4 ? 2 : 4;
 }

@@ -1,0 +1,18 @@
+"""A workspace sized for N tokens serves every smaller N: the sizes never fall as N
+grows, whichever tiles the library picks on the way (the input gradient's per-block
+sums take more blocks on some smaller N)."""
+import pytest
+import torch
+
+import paper_2606_10531_amd as lc
+
+
+@pytest.mark.parametrize("m,n", [(64, 64), (512, 28672), (28672, 512), (4096, 4096), (6280, 10136)])
+@pytest.mark.parametrize("op", [lc.OP_FWD, lc.OP_BWD])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_workspace_grows_with_tokens(op, m, n, dtype):
+    last = 0
+    for N in list(range(1, 700, 31)) + list(range(700, 16500, 257)):
+        size = lc.workspace_bytes(op, N, m, n, 8, dtype)
+        assert size >= last, f"N={N}"
+        last = size
