@@ -518,7 +518,7 @@ def main():
         return
     if args.gpus != 1:
         print(f"bench.py: this build runs on one GPU only (asked for --gpus {args.gpus}); the multi-GPU "
-              "sharding of the layer is described in DESIGN.md but not built.", file=sys.stderr)
+              "sharding of the layer is not built.", file=sys.stderr)
         sys.exit(2)
 
     import torch
