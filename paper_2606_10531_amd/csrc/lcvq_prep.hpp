@@ -130,7 +130,7 @@ hipError_t launch_fwd_bf16(const uint32_t *frag, const uint16_t *Xp, int64_t ldp
 // fixed order into dA and db (added to them when accumulating).  map_rows_max: the most
 // blocks that any tile gives, which grows with N and n where map_rows need not.
 int map_rows(int64_t N, int64_t m, int64_t n);
-inline int map_rows_max(int64_t N, int64_t n) { return (int)(ceil_div(n, 64) * ceil_div(N, 64)); }
+inline int64_t map_rows_max(int64_t N, int64_t n) { return ceil_div(n, 64) * ceil_div(N, 64); }
 hipError_t launch_dx_bf16(const uint32_t *frag, const uint16_t *dY, const float *rsp, const float *A, const float *b,
                           int d, uint16_t *dX, const uint16_t *X, float *mapp, int64_t N, int64_t m, int64_t n,
                           hipStream_t st);
