@@ -752,10 +752,13 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dw_half(const uint16_t *__restr
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // The waits count loads in issue order.  Prologue: B 0, A 0 (8), B 1, B 2 (4 each): at
-  // most 8 in flight holds B 0 complete wherever the compiler leaves the A loads.  Before
-  // the barrier of step k: behind B k + 1 at most A of k - 1 and k, B k + 2, A (k, 1) and
-  // A (k + 1, 0), of which the last three (12 loads) may be in flight.
+  // The waits count loads in issue order: the loads that are certain to lie behind the
+  // wanted ones may stay in flight, wherever the compiler leaves the prologue's A loads
+  // (it may sink them past the barrier, to their first use).  Prologue: B 0, A 0 (8), B 1,
+  // B 2 (4 each); step 0 reads both B 0 and, behind its own barrier, B 1, with only B 2
+  // and A (1, 0) issued after it, so the prologue waits for B 1 as well (4 left).  From
+  // step 1 on, before the barrier of step k: behind B k + 1 at least B k + 2, A (k, 1) and
+  // A (k + 1, 0), 12 loads.
   issue(0);
   load_a(0, 0);
   load_a(1, 0);
@@ -764,7 +767,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_dw_half(const uint16_t *__restr
   __builtin_amdgcn_sched_barrier(0);
   issue(2);
   __builtin_amdgcn_sched_barrier(0);
-  LCVQ_WAIT_VM_LGKM0(8);
+  LCVQ_WAIT_VM_LGKM0(4);
   LCVQ_BARRIER();
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
