@@ -184,10 +184,7 @@ __device__ __forceinline__ void quant_block(int bq, int by, int gx, const uint16
         }
         // masks: byte 4 kk + p of the row's 64-bit word, the quad's four bytes together
         auto mask_word = [&](const MaskRange &range) {
-          uint32_t mb = 0;
-#pragma unroll
-          for (int e = 7; e >= 0; --e) mask_push(mb, z[e], range);
-          return quad_or(in ? mb << (8 * p) : 0u);
+          return quad_or(in ? mask_byte(z, range) << (8 * p) : 0u);
         };
         if constexpr (kMode == kQuantBwd) {
           if (maskbits != nullptr) mr[rb][kk] = mask_word(mask_range(mask_mode));
