@@ -168,7 +168,8 @@ lcvq_status_t lcvq_encode(int64_t m, int64_t n, int32_t d, const void *W, int32_
  * (op = LCVQ_OP_FWD), lcvq_linear_bwd / lcvq_linear_bwd_dge (op = LCVQ_OP_BWD)
  * or lcvq_linear_fwd_packed (op = LCVQ_OP_FWD_PACKED, dtype LCVQ_BF16; it grows
  * with N above 16 tokens, up to 64 MiB, and a smaller one is accepted, see there)
- * for these sizes and element type.  Returns 0 for invalid arguments.  The workspace holds
+ * for these sizes and element type; a workspace for N tokens serves every smaller
+ * N as one of its own size would.  Returns 0 for invalid arguments.  The workspace holds
  * transient, library-private data (transformed activations, codes in the
  * matrix-core operand layout, per-token sums, partial sums of dA and db); its
  * contents are undefined between calls.
@@ -219,7 +220,8 @@ lcvq_status_t lcvq_linear_fwd_ex(int64_t N, int64_t m, int64_t n, int32_t d, int
  * packed codes (m * n / 4 bytes, the only large operand); more are taken in as few
  * passes as the workspace allows (2 n bytes per token, whole 64-token tiles), with
  * the same bits whatever the number of passes, or 16 at a time when it holds fewer
- * than 64 tokens.
+ * than 64 tokens (sums in another order: the last bits may differ from those of
+ * wide passes).
  *   N, m, n    tokens, out-features, in-features; d in {4, 8}
  *   packed     m * n / 4 bytes of codes (device, 16-byte aligned)
  *   A, b       map and offset, fp32 (device)

@@ -267,7 +267,7 @@ size_t lcvq_workspace_bytes(int32_t op, int64_t N, int64_t m, int64_t n, int32_t
   if (op == LCVQ_OP_BWD) return bwd_layout(N, m, n, bf16).total;
   if (op == LCVQ_OP_FWD_PACKED) {
     if (!bf16) return 0;
-    return up256((size_t)std::max(lcvq::packed_narrow(n).bytes, lcvq::packed_wide_plan(N, n, lcvq::kPackedWideBytes).bytes));
+    return up256((size_t)std::max(lcvq::packed_narrow(n).bytes, lcvq::packed_wide_bytes(N, n)));
   }
   return 0;
 }

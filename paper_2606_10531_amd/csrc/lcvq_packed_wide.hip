@@ -26,6 +26,8 @@
 // Bound: the matrix core where the tiles fill the chip, else operand latency.  The
 // 16-token passes that this replaces read the codes once per 16 tokens and took two
 // launches each: 512 tokens through 11008 x 4096 and 4096 x 11008 1033 us, now 86.
+#include <algorithm>
+
 #include "lcvq_mfma.hpp"
 #include "lcvq_prep.hpp"
 
@@ -258,19 +260,28 @@ __global__ __launch_bounds__(256, 2) void k_packed_wide(const uint8_t *__restric
 // Tokens per pass: as many whole 64-token tiles as `bytes` hold, in passes of equal
 // size.  A token's result does not depend on the pass or the tile it falls in (the
 // waves' shares of K, the order of their sums and the parts of s follow from n alone),
-// so every workspace gives the same bits.
+// so every workspace of at least 64 tokens gives the same bits; 16-token passes sum in
+// another order.
 PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes) {
   PackedWidePlan p{};
   p.KT = (int)ceil_div(n, kWk);
   p.spp = (int)ceil_div(p.KT, kMaxActChunks);
   p.parts = p.spp > 0 ? (int)ceil_div(p.KT, p.spp) : 0;
-  const int64_t per_token = (int64_t)p.KT * kWk * 2 + p.parts * 4;
-  const int64_t most = per_token > 0 ? bytes / per_token / 64 * 64 : 0;
+  p.per_token = (int64_t)p.KT * kWk * 2 + p.parts * 4;
+  const int64_t most = p.per_token > 0 ? bytes / p.per_token / 64 * 64 : 0;
   if (N <= 16 || most < 64) return p;  // T = 0: 16-token passes
   p.T = (int)round_up(ceil_div(N, ceil_div(N, most)), 64);
   p.sp = (int64_t)p.T * p.KT * kWk * 2;
-  p.bytes = p.sp + (int64_t)p.parts * p.T * 4;
+  p.bytes = p.T * p.per_token;
   return p;
+}
+
+// The most that any number of tokens up to N takes in a pass of up to kPackedWideBytes,
+// i.e. one pass while they fit, else the largest pass.
+int64_t packed_wide_bytes(int64_t N, int64_t n) {
+  const int64_t per_token = packed_wide_plan(1, n, 0).per_token;
+  if (N <= 16 || per_token == 0) return 0;
+  return std::min(round_up(N, 64), kPackedWideBytes / per_token / 64 * 64) * per_token;
 }
 
 hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int spp, int parts, int d, const float *A,

@@ -101,13 +101,15 @@ hipError_t launch_packed_fused(const PackedNarrow &p, const uint8_t *packed, int
 // The same for more than 16 tokens, T tokens per pass (lcvq_packed_wide.hip); T = 0:
 // not used (few tokens, or `bytes` of workspace do not hold 64 tokens' X').  The
 // workspace holds X' of a pass and, at byte sp, `parts` rows of T partial sums of s.
-// lcvq_workspace_bytes asks for one pass of all tokens up to kPackedWideBytes.
+// lcvq_workspace_bytes asks for packed_wide_bytes: one pass of all tokens, up to
+// kPackedWideBytes; it never falls as N grows.
 constexpr int64_t kPackedWideBytes = (int64_t)64 << 20;
 struct PackedWidePlan {
   int T, KT, spp, parts;  // tokens per pass, 256-wide steps, steps per part, parts of s
-  int64_t sp, bytes;
+  int64_t per_token, sp, bytes;
 };
 PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes);
+int64_t packed_wide_bytes(int64_t N, int64_t n);
 hipError_t launch_packed_wide(const PackedWidePlan &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc,
                               void *Y, bool y_bf16, hipStream_t st);
 

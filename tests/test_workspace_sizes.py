@@ -1,15 +1,16 @@
 """A workspace sized for N tokens serves every smaller N: the sizes never fall as N
 grows, whichever tiles the library picks on the way (the input gradient's per-block
-sums take more blocks on some smaller N)."""
+sums take more blocks on some smaller N; the packed forward takes many tokens in
+several passes of equal size, which are smaller than the one pass of fewer tokens)."""
 import pytest
 import torch
 
 import paper_2606_10531_amd as lc
 
 
-@pytest.mark.parametrize("m,n", [(64, 64), (512, 28672), (28672, 512), (4096, 4096), (6280, 10136)])
-@pytest.mark.parametrize("op", [lc.OP_FWD, lc.OP_BWD])
-@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("m,n", [(64, 64), (512, 28672), (28672, 512), (4096, 4096), (6280, 10136), (8192, 28672)])
+@pytest.mark.parametrize("op,dtype", [(op, dtype) for op in (lc.OP_FWD, lc.OP_BWD) for dtype in
+                                      (torch.bfloat16, torch.float32)] + [(lc.OP_FWD_PACKED, torch.bfloat16)])
 def test_workspace_grows_with_tokens(op, m, n, dtype):
     last = 0
     for N in list(range(1, 700, 31)) + list(range(700, 16500, 257)):
