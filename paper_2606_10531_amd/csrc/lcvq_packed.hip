@@ -13,20 +13,41 @@
 // Block: 16 MR weight rows; its kW waves split K (256-wide steps w, w + kW, ...) and
 // add their tiles in LDS at the end, in wave order.  No split over blocks, so no
 // second launch, counters or partial tiles in memory: small matrices get their
-// parallelism from short tiles and many waves.  Every wave has the codes of its next
-// step in flight while it works on the current one.
+// parallelism from short tiles and many waves.  Each wave has two stages: the loads of
+// its next step, X first, are issued before the current step is multiplied, and that
+// starts with X and takes two row blocks of codes at a time as they arrive, so that
+// little is left to do behind the last load.
 //
 // Up to four tokens, each wave transforms its own steps' X (its 64 lanes are the 16
 // column runs of four tokens, or half runs of two), and the call is one launch; above
 // that a prepass writes X' once (k_packed_xprep).
 //
-// Bound: the codes' bytes plus, after the last of them has arrived, the last step's
-// conversions and products (about 370 vector instructions per 64 rows x 256 columns);
-// at 16 tokens also the X' fragments from the L2, twice the codes' bytes with 64 rows.
+// Bound: the codes' bytes plus, after the last of them has arrived, two row blocks'
+// conversions and products and the waves' sum; at 16 tokens also the X' fragments from
+// the L2, twice the codes' bytes with 64 rows.
+#include <type_traits>
+#include <utility>
+
 #include "lcvq_mfma.hpp"
 #include "lcvq_prep.hpp"
 
 namespace lcvq {
+
+// At most N loads in flight; nothing moves across.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  LCVQ_WAIT_VM(N);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+template <int... I, class F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, I...>, F f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F f) {
+  static_for(std::make_integer_sequence<int, N>{}, f);
+}
 
 // kD: group size when the block transforms X itself, for up to kTok = 2 or 4 tokens;
 // 0 when X' and the parts of s are ready in xq and sp.
@@ -53,9 +74,11 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
   const uint32_t aoff = (uint32_t)(lrow * ldb + 16 * lpiece), astep = (uint32_t)(16 * ldb);
   const uint32_t roff = (uint32_t)(c16 * 64 + ((q ^ ((c16 >> 1) & 3)) << 4));
   auto load_a = [&](int st, int j) {
+    uint32_t base = (uint32_t)(wave * kStage + st * MR * 1024);
+    asm volatile("" : "+s"(base));  // the addresses are made here: held over the loop, they would crowd out A
 #pragma unroll
     for (int k = 0; k < MR; ++k)
-      buffer_to_lds16(rsA, (lds_void *)(stage + (st * MR + k) * 1024), j < KT ? aoff + k * astep + 64u * j : kOffNone);
+      buffer_to_lds16(rsA, (lds_void *)(lds + base + k * 1024), j < KT ? aoff + k * astep + 64u * j : kOffNone);
   };
   // X of a step: the operand fragments, or (fused) the 16 / kH columns that lane (run
   // L % 16, q = L / 16) transforms: token q / kH, part q % kH of the run's 16
@@ -64,8 +87,8 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
   u32x4 xr[2][kXL];
   auto load_x = [&](int buf, int j) {
     if constexpr (kFused) {
-      const int64_t c = (int64_t)j * 256 + 16 * c16 + 8 * h;
-      const uint32_t off = j < KT && tok < Nc && c < n ? (uint32_t)((tok * n + c) * 2) : kOffNone;
+      const int c = j * 256 + 16 * c16 + 8 * h;  // (steps past KT lie past n)
+      const uint32_t off = tok < Nc && c < (int)n ? (uint32_t)(tok * (int)n + c) * 2u : kOffNone;
 #pragma unroll
       for (int i = 0; i < kXL; ++i)
         xr[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(rsX, (int)(off == kOffNone ? kOffNone : off + 16u * i), 0, 0);
@@ -77,12 +100,14 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
                                                            0, 0);
     }
   };
+  float am[kD1][kD1], bm[kD1];  // (fused) the map, in scalar registers for all steps
   float s = 0.0f;
   const int xtok = kFused ? (c16 < Nc ? c16 : 0) : 0;  // absent tokens read the first one's X'
   floatx4 acc[MR];
 #pragma unroll
   for (int rb = 0; rb < MR; ++rb) acc[rb] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-  auto compute = [&](int u) {
+  // the step's X' operands: transformed here through the wave's LDS (fused), or as loaded
+  auto operands = [&](int u, u32x4 (&xf)[8]) __attribute__((always_inline)) {
     if constexpr (kFused) {
       constexpr int kC = 16 / kH;  // columns per lane
       float x[kXL * 8], y[kC];
@@ -98,9 +123,9 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
         for (int k = 0; k < kD1; ++k) {
           float v = 0.0f;
 #pragma unroll
-          for (int i = 0; i < kD1; ++i) v = fmaf(x[g * kD1 + i], A[i * kD1 + k], v);
+          for (int i = 0; i < kD1; ++i) v = fmaf(x[g * kD1 + i], am[i][k], v);
           y[g * kD1 + k] = v;
-          s = fmaf(x[g * kD1 + k], b[k], s);
+          s = fmaf(x[g * kD1 + k], bm[k], s);
         }
       // chunk (i, lane group, token) of 16 bytes: run c16 is lane group c16 / 4, dword
       // c16 % 4; this lane has its dwords kC / 4 h ..
@@ -112,41 +137,67 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
           p[16 * kTok + e] = pack_bf16x2(y[4 * e + 1], y[4 * e + 3]);
         }
       }
-    }
-    u32x4 a[MR];
 #pragma unroll
-    for (int rb = 0; rb < MR; ++rb) a[rb] = *reinterpret_cast<const u32x4 *>(stage + (u * MR + rb) * 1024 + roff);
+      for (int i = 0; i < 8; ++i) xf[i] = *reinterpret_cast<const u32x4 *>(xst + ((i * 4 + q) * kTok + xtok) * 16);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      u32x4 xf;
-      if constexpr (kFused) xf = *reinterpret_cast<const u32x4 *>(xst + ((i * 4 + q) * kTok + xtok) * 16);
-      else xf = xr[u][i];
-#pragma unroll
-      for (int rb = 0; rb < MR; ++rb) {
-        const uint32_t w = a[rb][i >> 1];
-        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nibbles_to_bf16x8(((i & 1) ? w >> 2 : w) & 0x33333333u),
-                                                          __builtin_bit_cast(bf16x8, xf), acc[rb], 0, 0, 0);
-      }
+      for (int i = 0; i < 8; ++i) xf[i] = xr[u][i];
     }
   };
-
-  load_a(0, wave);
-  load_x(0, wave);
-  __builtin_amdgcn_sched_barrier(0);
-  for (int j = wave; j < KT; j += 2 * kW) {
+  auto rows = [&](int u, int rb0, int nrb, const u32x4 (&xf)[8]) __attribute__((always_inline)) {
+    u32x4 a[MR];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (u == 1 && j + kW >= KT) break;
-      load_a(u ^ 1, j + (u + 1) * kW);
-      load_x(u ^ 1, j + (u + 1) * kW);
+    for (int rb = rb0; rb < rb0 + nrb; ++rb) a[rb] = *reinterpret_cast<const u32x4 *>(stage + (u * MR + rb) * 1024 + roff);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int rb = rb0; rb < rb0 + nrb; ++rb) {
+        const uint32_t w = a[rb][i >> 1];
+        acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nibbles_to_bf16x8(((i & 1) ? w >> 2 : w) & 0x33333333u),
+                                                          __builtin_bit_cast(bf16x8, xf[i]), acc[rb], 0, 0, 0);
+      }
+  };
+  // One step from stage u, with kLater younger loads in flight: X first, which its codes'
+  // loads follow, then two row blocks at a time as they arrive.
+  auto step = [&](auto later, int u) __attribute__((always_inline)) {
+    constexpr int kLater = decltype(later)::value;
+    u32x4 xf[8];
+    wait_vm<kLater + MR>();
+    operands(u, xf);
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<(MR + 2 - 1) / 2>([&](auto g) __attribute__((always_inline)) {
+      constexpr int rb = 2 * decltype(g)::value, n = MR - rb < 2 ? MR - rb : 2;
+      wait_vm<kLater + MR - rb - n>();
+      rows(u, rb, n, xf);
       __builtin_amdgcn_sched_barrier(0);
-      LCVQ_WAIT_VM(MR + kXL);  // all but the loads just issued: this step's codes are in LDS
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      compute(u);
-      __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  auto load = [&](int u, int j) __attribute__((always_inline)) {  // kXL + MR loads
+    load_x(u, j);
+    __builtin_amdgcn_sched_barrier(0);
+    load_a(u, j);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load(0, wave);
+  if constexpr (kFused) {  // (behind the first loads: nothing waits for it before they are out)
+#pragma unroll
+    for (int i = 0; i < kD1; ++i) {
+      bm[i] = b[i];
+#pragma unroll
+      for (int k = 0; k < kD1; ++k) am[i][k] = A[i * kD1 + k];
     }
   }
+  // Steps in pairs, the last of an odd number behind the loop.  There is no way out
+  // between the loads and the step they belong to: with one, the compiler had moved the
+  // loads behind it, or waited for all of them at the loop's head.
+  int j = wave;
+  for (; j + kW < KT; j += 2 * kW) {
+    load(1, j + kW);
+    step(std::integral_constant<int, MR + kXL>{}, 0);
+    load(0, j + 2 * kW);
+    step(std::integral_constant<int, MR + kXL>{}, 1);
+  }
+  if (j < KT) step(std::integral_constant<int, 0>{}, 0);
 
   // ------------------------------------------------------------ epilogue
   if constexpr (kFused) {  // over the runs and parts of a token: every lane of it has the sum
@@ -154,36 +205,41 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
     for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
     if constexpr (kH == 2) s += __shfl_xor(s, 16, 64);
   }
+  float st = 0.0f;
+  if constexpr (!kFused) {  // read here, under the waits: behind the sums it costs up to 1 us
+    if (c16 < Nc && wave < MR)
+      for (int p = 0; p < parts; ++p) st += sp[p * 16 + c16];
+  }
   LCVQ_WAIT_ALL();  // the last stage's loads have landed before the sums overwrite it
   __syncthreads();
   floatx4 *red = reinterpret_cast<floatx4 *>(lds);  // [wave][row block][lane]
   float *s_red = reinterpret_cast<float *>(lds + kW * MR * 1024);  // [wave][token]
+  if (c16 < Nc) {  // (absent tokens' columns are not summed)
 #pragma unroll
-  for (int rb = 0; rb < MR; ++rb) red[(wave * MR + rb) * 64 + lane] = acc[rb];
+    for (int rb = 0; rb < MR; ++rb) red[(wave * MR + rb) * 64 + lane] = acc[rb];
+  }
   if (kFused && c16 == 0 && h == 0) s_red[wave * 4 + tok] = s;
   __syncthreads();
-  if (wave >= MR) return;
-  // thread (rb = wave, lane): rows 16 rb + 4 q + (0..3), token L % 16
-  floatx4 v = red[wave * 64 + lane];
-#pragma unroll
-  for (int w = 1; w < kW; ++w) v += red[(w * MR + wave) * 64 + lane];
-  const int64_t row = r0 + 16 * wave + 4 * q;  // m is a multiple of 8: the four rows are all in or all out
-  if (c16 >= Nc || row >= m) return;
-  float st = 0.0f;
   if constexpr (kFused) {
 #pragma unroll
     for (int w = 0; w < kW; ++w) st += s_red[w * 4 + (c16 & 3)];
-  } else {
-    for (int p = 0; p < parts; ++p) st += sp[p * 16 + c16];
   }
-  const int64_t o = (int64_t)c16 * m + row;
-  if (y_bf16) {
-    uint2 w;
-    w.x = pack_bf16x2(v[0] + st, v[1] + st);
-    w.y = pack_bf16x2(v[2] + st, v[3] + st);
-    *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Y) + o) = w;
-  } else {
-    *reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(Y) + o) = v + st;
+  // thread (rb, lane): rows 16 rb + 4 q + (0..3), token L % 16
+  for (int rb = wave; rb < MR; rb += kW) {
+    const int64_t row = r0 + 16 * rb + 4 * q;  // m is a multiple of 8: the four rows are all in or all out
+    if (c16 >= Nc || row >= m) return;
+    floatx4 v = red[rb * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < kW; ++w) v += red[(w * MR + rb) * 64 + lane];
+    const int64_t o = (int64_t)c16 * m + row;
+    if (y_bf16) {
+      uint2 w;
+      w.x = pack_bf16x2(v[0] + st, v[1] + st);
+      w.y = pack_bf16x2(v[2] + st, v[3] + st);
+      *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Y) + o) = w;
+    } else {
+      *reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(Y) + o) = v + st;
+    }
   }
 }
 
@@ -192,29 +248,46 @@ bool packed_fused(int Nc) { return Nc <= 4; }
 
 // Rows per block: 16 MR with the fewest rounds of blocks over the 256 compute units and
 // those rounds full, MR at most 8, so that every unit gets the same share of the codes
-// and reads or makes the X' of a step once per round (28672 x 8192 at one token: MR 4,
-// 7 blocks for every 4 units, 20.4 us, MR 7, one for each, 17.6; 11008 x 4096: 7.3 with
-// MR 4, 6.7 with 3; 8192 x 28672: 25.2 with 4, 18.7 with 2 and sixteen waves).  Sixteen
-// waves where a block's rows are few and K gives each of them about two steps (4096 x
-// 11008 7.3 -> 6.9, 4096 x 4096 4.4 against 4.5 without).
-// Before (64-row blocks of four waves, K split over blocks, a prepass except for long
-// rows): one token through 28672 x 8192 19.5, 8192 x 28672 24.7, 4096 x 11008 13.1,
-// 11008 x 4096 15.1, 4096 x 4096 10.8 us, now 17.6, 18.7, 6.9, 6.7 and 4.4; 16 tokens 26.8,
-// 33.2, 15.5, 19.9 and 12.5, now 23.4, 30.5, 14.4, 12.1 and 9.6.
+// and reads or makes the X' of a step once per round (28672 x 8192: MR 7, one block for
+// each unit; with MR 4, 7 blocks for every 4 units, 16.6 us against 16.7 at one token, but
+// 11008 x 4096 7.3 against 6.7 with 3 and 8192 x 28672 23.1 against 16.4 with 2).
+// Waves: sixteen where a block's rows are few and K gives each of them about two steps
+// (4096 x 11008 7.3 -> 6.9, 4096 x 4096 4.4 against 4.5 without).  Four where the block
+// transforms X itself, has 64 rows or more and K is 16 to 63 steps, so that each wave has
+// four or more of them: longer chains of steps hide the waits better than more waves (one
+// token, eight -> four waves: 28672 x 8192 16.6 -> 15.2 us, 20480 x 4096 8.6 -> 7.6, 16384 x
+// 6144 9.0 -> 8.6; but 28672 x 2048, eight steps in all, 6.5 -> 6.9, 32768 x 16384 34.9 ->
+// 35.8, 8192 x 8192 with 32 rows 7.0 -> 7.6).  Eight elsewhere.
+// Against 64-row blocks of four waves with K split over blocks and a prepass except for
+// long rows (one graph of calls, weights from memory, us): one token through 28672 x 8192
+// 16.1 -> 15.7, 8192 x 28672 23.1 -> 16.8, 4096 x 11008 13.0 -> 6.6, 11008 x 4096 14.7 -> 6.0,
+// 4096 x 4096 10.7 -> 4.1; 16 tokens 25.7 -> 22.4, 32.7 -> 28.7, 15.4 -> 13.6, 20.2 -> 11.4 and
+// 12.5 -> 9.4.
 template <int kD, int kTok>
 static hipError_t launch(const uint8_t *packed, int64_t m, int64_t n, const PackedNarrow &p, const uint16_t *xq,
                          const float *sp, const uint16_t *X, const float *A, const float *b, int Nc, void *Y, bool y_bf16,
                          hipStream_t st) {
   const int64_t rb = ceil_div(m, 16), rounds = ceil_div(rb, 256 * 8);
   const int mr = (int)ceil_div(rb, 256 * rounds);
-  const bool w16 = mr <= 2 && p.KT >= 24;
   using K = decltype(&k_packed<1, 8, kD, kTok>);
   static constexpr K k8[8] = {k_packed<1, 8, kD, kTok>, k_packed<2, 8, kD, kTok>, k_packed<3, 8, kD, kTok>,
                               k_packed<4, 8, kD, kTok>, k_packed<5, 8, kD, kTok>, k_packed<6, 8, kD, kTok>,
                               k_packed<7, 8, kD, kTok>, k_packed<8, 8, kD, kTok>};
-  const K k = w16 ? (mr == 2 ? k_packed<2, 16, kD, kTok> : k_packed<1, 16, kD, kTok>) : k8[mr - 1];
-  k<<<(unsigned)ceil_div(rb, mr), w16 ? 1024 : 512, 0, st>>>(packed, m, n, p.KT, xq, sp, p.parts, X, A, b, Nc, Y,
-                                                             y_bf16 ? 1 : 0);
+  K k = k8[mr - 1];
+  int waves = 8;
+  if (mr <= 2 && p.KT >= 24) {
+    k = mr == 2 ? k_packed<2, 16, kD, kTok> : k_packed<1, 16, kD, kTok>;
+    waves = 16;
+  }
+  if constexpr (kD > 0) {
+    static constexpr K k4[5] = {k_packed<4, 4, kD, kTok>, k_packed<5, 4, kD, kTok>, k_packed<6, 4, kD, kTok>,
+                                k_packed<7, 4, kD, kTok>, k_packed<8, 4, kD, kTok>};
+    if (mr >= 4 && p.KT >= 16 && p.KT < 64) {
+      k = k4[mr - 4];
+      waves = 4;
+    }
+  }
+  k<<<(unsigned)ceil_div(rb, mr), 64 * waves, 0, st>>>(packed, m, n, p.KT, xq, sp, p.parts, X, A, b, Nc, Y, y_bf16 ? 1 : 0);
   return hipGetLastError();
 }
 

@@ -1,4 +1,4 @@
-"""The packed-codes forward up to 16 tokens on each of its blocks (16 to 128 rows, 8
+"""The packed-codes forward up to 16 tokens on each of its blocks (16 to 128 rows, 4, 8
 and 16 waves, one and two rounds of blocks), with X transformed in the block (up to 2, up to 4 tokens) and by the
 prepass (5 and more), at ragged rows and K not a multiple of a step, with fewer steps
 than waves and with several per wave, against the oracle at 2e-2; a repeated call
@@ -45,3 +45,28 @@ def test_packed_rows(lc, N, m, n, d):
     ref = orc.linear_forward_packed(P, A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
     assert_close(to_host(got[0]), ref, 2e-2, "Y")
     assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4])
+@pytest.mark.parametrize("m,n,d", [(16376, 4096, 4), (16392, 4160, 8), (24568, 4544, 4), (28664, 8192, 8), (32776, 5184, 8),
+                                   (32760, 16064, 4)])
+def test_packed_rows_four_waves(lc, N, m, n, d):
+    """Blocks of 64 rows and more over 16 to 63 steps of K (four waves, an odd and an even
+    number of steps each), on sampled rows."""
+    import torch
+    print(f"\npacked rows, four waves N={N} m={m} n={n} d={d}", flush=True)
+    r = synth.rng(N + m + n + d)
+    P = r.integers(0, 256, size=(m, n // 4), dtype=np.uint8)
+    Xb = synth.draw_activations(N, n, 7 + N, "bf16")
+    A, b = synth.draw_map(d, 1)
+    Pd, X = torch.from_numpy(P).cuda(), to_dev(Xb, "bf16")
+    Ad, bd = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    got = []
+    for _ in range(3):
+        Y = torch.full((N, m), float("nan"), dtype=torch.float32, device="cuda")
+        got.append(lc.linear_fwd_packed(Pd, Ad, bd, X, d, out=Y))
+    torch.cuda.synchronize()
+    rows = np.unique(np.concatenate([np.arange(260), np.arange(m // 2, m // 2 + 260), np.arange(m - 260, m)]))
+    ref = orc.linear_forward_packed(P[rows], A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
+    assert_close(to_host(got[0])[:, rows], ref, 2e-2, "Y")
+    assert all(torch.equal(got[0].view(torch.int32), g.view(torch.int32)) for g in got[1:])
