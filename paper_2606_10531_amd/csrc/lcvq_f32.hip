@@ -27,6 +27,9 @@
 namespace lcvq {
 
 constexpr int64_t kMaxBufLd = (int64_t)1 << 22;  // 64 rows of 2^22 floats: 2^30 bytes
+// One dimension of a grid holds fewer than 2^32 threads: tiles past this many go on in
+// the grid's next row (2^35 outputs of the forward are that many).
+constexpr int kGridRow = 1 << 23;
 constexpr int kFM = 32, kFK = 64;   // tile rows, K chunk
 constexpr int kLdK = kFK + 4;       // LDS row of a K-contiguous operand: 16-byte reads of 8 rows meet 8 bank groups
 constexpr int kLdM = kFM + 4;       // LDS row (one k) of an M-contiguous operand: k rows four apart are 16 banks apart
@@ -74,7 +77,7 @@ __global__ __launch_bounds__(256) void k_f32(const float *__restrict__ Z, Quanti
                                              const float *__restrict__ dY, const float *__restrict__ A,
                                              const float *__restrict__ bvec, int64_t N, int64_t m, int64_t n, int tiles_n,
                                              int mask_mode, GradEst est, int accumulate, float *__restrict__ out,
-                                             float *__restrict__ mapp, const float *__restrict__ svec) {
+                                             float *__restrict__ mapp, const float *__restrict__ svec, int tiles) {
   constexpr int kN = 16 * NB, kLdN = kN + 4;
   constexpr bool kFwd = kMode == 0 || kMode == 3;
   constexpr int kASize = kFwd ? kFM * kLdK : kFK * kLdM;
@@ -85,7 +88,10 @@ __global__ __launch_bounds__(256) void k_f32(const float *__restrict__ Z, Quanti
   __shared__ float srow[kN];  // s of the forward, rowsum(dY) of the input gradient
   const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * kFM, n0 = (int64_t)(blockIdx.x % tiles_n) * kN;
+  // (the last grid row may have blocks past the last tile: they find no rows to load or
+  // store; leaving at once would wait for `tiles` before anything else, 0.2 us a launch)
+  const unsigned tile = blockIdx.y * (unsigned)kGridRow + blockIdx.x;
+  const int64_t m0 = (int64_t)(tile / (unsigned)tiles_n) * kFM, n0 = (int64_t)(tile % (unsigned)tiles_n) * kN;
   const int64_t K = kFwd ? n : kMode == 1 ? m : N;
   const int64_t Mlen = kFwd ? m : n, Nlen = kMode == 2 ? m : N;
 
@@ -385,11 +391,11 @@ __global__ __launch_bounds__(256) void k_f32(const float *__restrict__ Z, Quanti
       if (c16 == 0) p[D * D + i % D] = dbv[e];
     }
     __syncthreads();
-    if (tid < D * D + D) {
+    if (tid < D * D + D && tile < (unsigned)tiles) {
       float t = 0.0f;
 #pragma unroll
       for (int w = 0; w < 4 * kSlots; ++w) t += sum[w * (D * D + D) + tid];
-      mapp[(int64_t)tid * gridDim.x + blockIdx.x] = t;  // summed over the blocks by launch_map_combine
+      mapp[(int64_t)tid * tiles + tile] = t;  // summed over the blocks by launch_map_combine
     }
   }
 }
@@ -448,8 +454,9 @@ static hipError_t launch(const float *Z, const Quantizer &qz, const float *X, co
                 : (vec ? k_f32<kMode, D, 2, true, true> : k_f32<kMode, D, 2, false, true>);
   // rows so long that a tile's offsets pass 2^31
   if (m >= kMaxBufLd || n >= kMaxBufLd) k = wide ? k_f32<kMode, D, 4, false, false> : k_f32<kMode, D, 2, false, false>;
-  k<<<(unsigned)(tm * tn), 256, 0, st>>>(Z, qz, X, dY, A, b, N, m, n, (int)tn, mask_mode, est, accumulate, out, mapp,
-                                          svec);
+  const int64_t tiles = tm * tn;
+  const dim3 grid((unsigned)(tiles < kGridRow ? tiles : kGridRow), (unsigned)ceil_div(tiles, kGridRow));
+  k<<<grid, 256, 0, st>>>(Z, qz, X, dY, A, b, N, m, n, (int)tn, mask_mode, est, accumulate, out, mapp, svec, (int)tiles);
   return hipGetLastError();
 }
 

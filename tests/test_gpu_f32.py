@@ -72,3 +72,25 @@ def test_f32_rows_past_the_buffer_offsets(lc):
             assert_close(to_host(dX), orc.grad_input(v["dY"], W), TOL, "dX")
             assert_close(to_host(dZ), orc.grad_latent(orc.grad_weight(v["dY"], v["X"]), v["A"], 8,
                                                       orc.ste_mask(v["Z"])), TOL, "dZ")
+
+
+def test_f32_output_of_more_tiles_than_one_grid_row(lc):
+    """2^35 outputs and more: the tiles' threads pass 2^32, the most of one grid dimension."""
+    import torch
+    N, m, n, d = 4194048, 8200, 8, 8
+    print(f"\nf32 N={N} m={m} n={n}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Z = torch.empty((m, n), device="cuda").uniform_(-1.0, 4.0, generator=g)
+    X = torch.randn((N, n), device="cuda", generator=g)
+    A = 0.02 * (torch.eye(d, device="cuda") + 0.1 * torch.randn((d, d), device="cuda", generator=g))
+    b = 0.005 * torch.randn((d,), device="cuda", generator=g)
+    Y = torch.empty((N, m), device="cuda")
+    Y[-1] = float("nan")
+    lc.linear_fwd(Z, A, b, X, d, out=Y)
+    torch.cuda.synchronize()
+    rows = torch.cat([torch.arange(64), torch.arange(N // 2, N // 2 + 64), torch.arange(N - 300, N)])
+    W = orc.decode(orc.quantize(to_host(Z)), to_host(A), to_host(b), d)
+    got, ref = to_host(Y[rows.cuda()]), orc.forward(to_host(X[rows.cuda()]), W)
+    del Y
+    torch.cuda.empty_cache()
+    assert_close(got, ref, TOL, "Y")
