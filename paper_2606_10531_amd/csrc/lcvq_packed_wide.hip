@@ -257,6 +257,11 @@ __global__ __launch_bounds__(256, 2) void k_packed_wide(const uint8_t *__restric
   }
 }
 
+// Most tokens of a pass: its grid has a thread per 16 outputs (64-row tiles), which for the
+// most out-features (2^21) has to stay below 2^32.  (In-features of 1024 or more hit the
+// workspace limit first.)
+constexpr int64_t kMaxPassTokens = (int64_t)1 << 15;
+
 // Tokens per pass: as many whole 64-token tiles as `bytes` hold, in passes of equal
 // size.  A token's result does not depend on the pass or the tile it falls in (the
 // waves' shares of K, the order of their sums and the parts of s follow from n alone),
@@ -268,7 +273,7 @@ PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes) {
   p.spp = (int)ceil_div(p.KT, kMaxActChunks);
   p.parts = p.spp > 0 ? (int)ceil_div(p.KT, p.spp) : 0;
   p.per_token = (int64_t)p.KT * kWk * 2 + p.parts * 4;
-  const int64_t most = p.per_token > 0 ? bytes / p.per_token / 64 * 64 : 0;
+  const int64_t most = p.per_token > 0 ? std::min(bytes / p.per_token / 64 * 64, kMaxPassTokens) : 0;
   if (N <= 16 || most < 64) return p;  // T = 0: 16-token passes
   p.T = (int)round_up(ceil_div(N, ceil_div(N, most)), 64);
   p.sp = (int64_t)p.T * p.KT * kWk * 2;
@@ -281,7 +286,7 @@ PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes) {
 int64_t packed_wide_bytes(int64_t N, int64_t n) {
   const int64_t per_token = packed_wide_plan(1, n, 0).per_token;
   if (N <= 16 || per_token == 0) return 0;
-  return std::min(round_up(N, 64), kPackedWideBytes / per_token / 64 * 64) * per_token;
+  return std::min({round_up(N, 64), kPackedWideBytes / per_token / 64 * 64, kMaxPassTokens}) * per_token;
 }
 
 hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int spp, int parts, int d, const float *A,

@@ -1,7 +1,8 @@
 """The packed-codes forward for more than 16 tokens (one pass over the codes per
 workspace of tokens), through the C ABI, against the oracle at 2e-2: tiles of 64 and
 of 128 rows, ragged rows and tokens, K shorter than the four waves' steps and not a
-multiple of a step, several passes (28672 in-features at 200 tokens), both output
+multiple of a step, several passes (28672 in-features at 200 tokens with 8 MiB, 33000
+tokens), both output
 types.  The scratch-array call must give the same bits, and a workspace sized for
 fewer tokens is still accepted (16-token passes)."""
 import numpy as np
@@ -26,7 +27,7 @@ def lc():
 
 
 SHAPES = [(17, 8, 64, 8), (64, 72, 320, 4), (65, 200, 4160, 8), (130, 1032, 768, 4), (300, 4104, 512, 8),
-          (200, 264, 28672, 8)]
+          (200, 264, 28672, 8), (33000, 72, 64, 8)]
 
 
 @pytest.mark.parametrize("y_dtype", ["bf16", "f32"])

@@ -17,3 +17,13 @@ def test_workspace_grows_with_tokens(op, m, n, dtype):
         size = lc.workspace_bytes(op, N, m, n, 8, dtype)
         assert size >= last, f"N={N}"
         last = size
+
+
+def test_packed_passes_fit_one_grid():
+    """A pass of the packed forward is one grid of a thread per 16 outputs (at least); even
+    with the most out-features it stays below the 2^32 threads of a grid dimension, so the
+    tokens of a pass, which the size tells, stop at 2^15."""
+    m, n = (1 << 21) - 64, 64
+    one = lc.workspace_bytes(lc.OP_FWD_PACKED, 64, m, n, 8, torch.bfloat16) / 64
+    tokens = lc.workspace_bytes(lc.OP_FWD_PACKED, 1 << 20, m, n, 8, torch.bfloat16) / one
+    assert tokens * m / 16 < 2 ** 32
