@@ -419,7 +419,7 @@ typedef enum {
   LCVQ_K_DEQUANT = 6,   /* lcvq_dequant */
   LCVQ_K_FILL = 7,      /* zero fills of degenerate shapes */
   LCVQ_K_ADAM = 8,      /* lcvq_adamw_step */
-  LCVQ_K_PACKED_PREP = 9,  /* lcvq_linear_fwd_packed: X' and s of up to 16 tokens */
+  LCVQ_K_PACKED_PREP = 9,  /* lcvq_linear_fwd_packed: X' and s of a pass */
   LCVQ_K_PACKED = 10,      /* lcvq_linear_fwd_packed: Y from the packed codes */
   LCVQ_K_ENCODE = 11,      /* lcvq_encode */
   LCVQ_K_MAP_SUM = 12,     /* backward: dA, db, summed over the blocks of the product that forms them */
@@ -427,6 +427,16 @@ typedef enum {
 } lcvq_kernel_t;
 lcvq_status_t lcvq_timer_enable(uint32_t mask);
 lcvq_status_t lcvq_timer_read(int32_t kernel, double *total_ms, int64_t *launches);
+
+/*
+ * lcvq_product_tile -- which block tile a bf16 product takes at these sizes, as its
+ * number of weight-side rows, so that a test can say which kernel it runs:
+ *   LCVQ_K_FWD  out-features per block: 512 (k_gemm_codes), 128 or 64 (k_codes_split)
+ *   LCVQ_K_DX   in-features: 256 (k_gemm_codes), 128 or 64 (k_codes_split)
+ *   LCVQ_K_DW   out-features: 256 (k_gemm_dw), 128 (k_gemm_dw_half) or 64 (k_gemm_dw_split)
+ * 0 for other kernels and sizes that the products do not take.  Host arithmetic only.
+ */
+int32_t lcvq_product_tile(int32_t kernel, int64_t N, int64_t m, int64_t n);
 
 /* Static description of a status code. */
 const char *lcvq_status_string(lcvq_status_t status);

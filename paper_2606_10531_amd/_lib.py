@@ -56,6 +56,7 @@ SIGNATURES = {
     "lcvq_xavier_init": (_I32, [_I64, _I64, _I32, _P, _P, _I32, _P]),
     "lcvq_timer_enable": (_I32, [ctypes.c_uint32]),
     "lcvq_timer_read": (_I32, [_I32, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]),
+    "lcvq_product_tile": (_I32, [_I32, _I64, _I64, _I64]),
     "lcvq_status_string": (ctypes.c_char_p, [_I32]),
     "lcvq_last_error": (ctypes.c_char_p, []),
 }

@@ -781,6 +781,14 @@ lcvq_status_t lcvq_linear_bwd_dge(int64_t N, int64_t m, int64_t n, int32_t d, in
                     dA, db, workspace, workspace_bytes, stream);
 }
 
+int32_t lcvq_product_tile(int32_t kernel, int64_t N, int64_t m, int64_t n) {
+  if (N < 1 || m < 1 || n < 1 || N > kMaxTokens || m >= kMaxLd || n >= kMaxLd) return 0;
+  if (kernel == LCVQ_K_DW) return lcvq::dw_tile_rows(N, m, n);
+  if (kernel != LCVQ_K_FWD && kernel != LCVQ_K_DX) return 0;
+  const int slabs = kernel == LCVQ_K_FWD ? lcvq::fwd_slabs(N, m, n) : lcvq::dx_slabs(N, m, n);
+  return slabs ? 32 * slabs : kernel == LCVQ_K_FWD ? 512 : 256;
+}
+
 size_t lcvq_saved_bytes(int64_t N, int64_t m, int64_t n, int32_t d, int32_t dtype) {
   if (N < 0 || m < 0 || n < 0 || (d != 4 && d != 8) || dtype != LCVQ_BF16) return 0;
   return saved_layout(N, m, n).total;

@@ -1037,6 +1037,10 @@ static DwTile dw_tile(int64_t m, int64_t n, int64_t KBt) {
                 split = cost({1030, 2800, 670, 1800, 580, 300, 4600}, ceil_div(n, 128) * ceil_div(m, 64), KBt / 4);
   return full <= half && full <= split ? kDwFull : half <= split ? kDwHalf : kDwSplit;
 }
+int dw_tile_rows(int64_t N, int64_t m, int64_t n) {
+  const DwTile t = dw_tile(m, n, bwd_tokens(N) / 64);
+  return t == kDwSplit ? 64 : t == kDwHalf ? 128 : 256;
+}
 
 hipError_t launch_dw_bf16(const uint16_t *xt, const uint16_t *dyt, const uint64_t *maskbits, const uint16_t *Z,
                           const Quantizer &qz, int mask_mode, const GradEst &est, int accumulate, void *dZ,

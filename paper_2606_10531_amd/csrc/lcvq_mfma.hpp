@@ -7,9 +7,6 @@
 
 namespace lcvq {
 
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
-
 constexpr int kTile = 256;   // block tile (M and N)
 constexpr int kKStep = 64;   // K per main-loop step
 

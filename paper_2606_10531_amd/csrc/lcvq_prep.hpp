@@ -154,6 +154,8 @@ hipError_t launch_dx_split(int slabs, const uint32_t *frag, const uint16_t *dY, 
 hipError_t launch_dw_bf16(const uint16_t *xt, const uint16_t *dyt, const uint64_t *maskbits, const uint16_t *Z,
                           const Quantizer &qz, int mask_mode, const GradEst &est, int accumulate, void *dZ,
                           bool dz_bf16, int64_t N, int64_t m, int64_t n, hipStream_t st);
+// out-features of the tile that the weight gradient takes: 256, 128 or 64
+int dw_tile_rows(int64_t N, int64_t m, int64_t n);
 
 // fp32 products (lcvq_f32.hip).  The weight gradient's map_rows_f32(m, n) blocks
 // store their partial sums of dA and db as the bf16 path's input gradient does

@@ -21,6 +21,13 @@ def to_host(t):
     return t.numpy().astype(np.float64)
 
 
+def product_tile(kernel, N, m, n):
+    """Weight-side rows of the block tile that a bf16 product ("fwd", "dx" or "dw") takes at
+    these sizes: a test that is there for one kernel says so, and fails if the choice moves."""
+    from paper_2606_10531_amd import _lib
+    return _lib.load().lcvq_product_tile(_lib.KERNELS.index(kernel), N, m, n)
+
+
 def rel_fro(got, ref):
     got, ref = np.asarray(got, np.float64), np.asarray(ref, np.float64)
     den = np.linalg.norm(ref)

@@ -33,6 +33,16 @@ def test_every_declared_symbol_is_exported(lib):
     assert set(names) == set(L.SIGNATURES)
 
 
+def test_product_tile(lib):
+    """The tile query: the benchmarked layer on the wide tiles, 0 where no product runs."""
+    f, K = lib.lcvq_product_tile, L.KERNELS.index
+    assert [f(K(k), 4096, 4096, 4096) for k in ("fwd", "dx", "dw")] == [512, 256, 256]
+    assert [f(K(k), 1, 8, 8) for k in ("fwd", "dx", "dw")] == [64, 64, 64]
+    assert f(K("pack"), 4096, 4096, 4096) == 0 and f(-1, 1, 8, 8) == 0
+    for N, m, n in ((0, 8, 8), (8, 0, 8), (8, 8, -8), (1 << 22, 8, 8), (8, 1 << 21, 8), (8, 8, 1 << 21)):
+        assert f(K("dw"), N, m, n) == 0
+
+
 def test_status_strings(lib):
     for s in range(6):
         assert L.status_string(s)

@@ -1,6 +1,7 @@
 """The weight-gradient product on each of its tiles (128 x 64 with split tokens, 256 x
 128, 256 x 256), ragged on every side, against the oracle on sampled out-feature rows:
-both estimators, dZ in bf16 and fp32, overwritten and accumulated; and the same bits
+both estimators, dZ in bf16 and fp32, overwritten and accumulated; each shape has to
+take the tile it is there for; and the same bits
 over repeated calls (the two larger tiles stage an operand through LDS with explicit
 waits)."""
 import numpy as np
@@ -8,7 +9,7 @@ import pytest
 
 import oracle as orc
 import synth
-from helpers import assert_close, to_dev, to_host
+from helpers import assert_close, product_tile, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -24,16 +25,19 @@ def lc():
     return lc
 
 
-# split tokens: one, one step per wave and several; then 256 x 128 (289 tiles of 256 x 256
-# would take two rounds), then 256 x 256 (one full round)
-SHAPES = [(1, 8, 8, 8), (130, 72, 136, 4), (600, 200, 392, 8), (250, 4104, 4104, 8), (4000, 4040, 4072, 4)]
+# out-features of the tile: 64, tokens split over the waves (one token, one step per wave,
+# several); 128 with 4 steps of 64 tokens, where no LDS stage is refilled, and with 16; 256
+# with 24 steps, about the fewest it is taken for, and with 64 (one full round of tiles)
+SHAPES = [(1, 8, 8, 8, 64), (130, 72, 136, 4, 64), (600, 200, 392, 8, 64), (250, 4104, 4104, 8, 128),
+          (1000, 4104, 4104, 4, 128), (1526, 28168, 264, 8, 256), (4000, 4040, 4072, 4, 256)]
 
 
-@pytest.mark.parametrize("N,m,n,d", SHAPES)
+@pytest.mark.parametrize("N,m,n,d,tile", SHAPES)
 @pytest.mark.parametrize("est,dz,accumulate", [("ste", "bf16", False), ("ste", "f32", True), ("dge", "f32", False),
                                                ("dge", "bf16", True)])
-def test_dw_on_every_tile(lc, N, m, n, d, est, dz, accumulate):
+def test_dw_on_every_tile(lc, N, m, n, d, tile, est, dz, accumulate):
     import torch
+    assert product_tile("dw", N, m, n) == tile
     print(f"\ndw tiles N={N} m={m} n={n} d={d} {est} {dz} {accumulate}", flush=True)
     inp = synth.layer_inputs(N, m, n, d, "bf16", k=N + m + n + d, z_lo=-1.0, z_hi=4.0)
     Z, X, dY = (to_dev(inp[k], "bf16") for k in ("Z", "X", "dY"))

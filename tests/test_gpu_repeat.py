@@ -5,13 +5,15 @@ wait that no longer covers a stage shows up as a result that changes from one
 identical call to the next.  Every output is computed in a fixed order (dA and
 db as per-block partial sums added up in a fixed order, no atomics), so Y, the
 packed codes, dX, dZ, dA and db must all be the same bit for bit over repeated
-calls on the same inputs.  The shapes cover the weight-gradient loop with no
-full trip (256 tokens), a few trips and a ragged tail, and the 4096 x 4096 step
-of the benchmark, under both estimators."""
+calls on the same inputs.  The shapes cover every tile of the products: the
+weight gradient with its tokens split over the waves (256^3, 1024^3, ragged), on
+256 x 128 tiles with 16 steps and on 256 x 256 with 24 (the LDS stages of both are
+refilled many times over), the small tiles of the other products, and the 4096 x 4096
+step of the benchmark on the wide ones, under both estimators."""
 import pytest
 
 import synth
-from helpers import to_dev
+from helpers import product_tile, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -30,13 +32,17 @@ def _bits(t):
     return t.view(torch.int16 if t.dtype == torch.bfloat16 else (torch.uint8 if t.dtype == torch.uint8 else torch.int32))
 
 
-CASES = [(256, 256, 256, 8, 40), (1024, 1024, 1024, 8, 40), (1000, 520, 1096, 4, 40), (4096, 4096, 4096, 8, 60)]
+# the last three: weight-side rows of the tiles of the forward, the input and the weight gradient
+CASES = [(256, 256, 256, 8, 40, 64, 64, 64), (1024, 1024, 1024, 8, 40, 64, 64, 64), (1000, 520, 1096, 4, 40, 64, 128, 64),
+         (1000, 4104, 4104, 8, 40, 128, 128, 128), (1526, 28168, 264, 4, 40, 512, 64, 256), (744, 1032, 11072, 8, 40, 64, 256, 128),
+         (4096, 4096, 4096, 8, 60, 512, 256, 256)]
 
 
-@pytest.mark.parametrize("N,m,n,d,reps", CASES)
+@pytest.mark.parametrize("N,m,n,d,reps,tile_fwd,tile_dx,tile_dw", CASES)
 @pytest.mark.parametrize("est", ["ste", "dge"])
-def test_training_step_repeats_bit_for_bit(lc, N, m, n, d, reps, est):
+def test_training_step_repeats_bit_for_bit(lc, N, m, n, d, reps, tile_fwd, tile_dx, tile_dw, est):
     import torch
+    assert tuple(product_tile(k, N, m, n) for k in ("fwd", "dx", "dw")) == (tile_fwd, tile_dx, tile_dw)
     print(f"\nrepeat N={N} m={m} n={n} d={d} est={est} reps={reps}", flush=True)
     inp = synth.layer_inputs(N, m, n, d, "bf16", k=N + m + n + d, z_lo=-1.0, z_hi=4.0)
     Z, X, dY = to_dev(inp["Z"], "bf16"), to_dev(inp["X"], "bf16"), to_dev(inp["dY"], "bf16")

@@ -6,7 +6,12 @@ their block tiles, at sizes where a tile can go wrong, against the oracle.
   * small tiles of 128 rows (520 tokens, 2056 features: more than 256 tiles of 64
     rows, fewer of 128), ragged on every side;
   * wide tiles, ragged on every side (4000 tokens, 4040 x 4072: every tile of one
-    round busy), on sampled rows.
+    round busy), on sampled rows;
+  * the wide input gradient with K shorter than the 32 steps in which it fetches its X
+    tile (1032 and 72 out-features), so that the rest comes behind the loop.
+
+Each shape has to take the tiles it is there for (weight-side rows, forward and input
+gradient).
 
 Tolerance as everywhere for bf16: 2e-2 of the result, of every row and tile."""
 import numpy as np
@@ -14,7 +19,7 @@ import pytest
 
 import oracle as orc
 import synth
-from helpers import assert_close, to_dev, to_host
+from helpers import assert_close, product_tile, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -30,13 +35,16 @@ def lc():
     return lc
 
 
-SHAPES = [(1, 8, 64, 8), (64, 64, 64, 8), (65, 72, 328, 4), (200, 4104, 520, 8), (130, 136, 4616, 4),
-          (17, 1032, 1160, 8), (520, 2056, 2056, 8), (520, 2056, 2056, 4), (4000, 4040, 4072, 4)]
+SHAPES = [(1, 8, 64, 8, 64, 64), (64, 64, 64, 8, 64, 64), (65, 72, 328, 4, 64, 64), (200, 4104, 520, 8, 64, 64),
+          (130, 136, 4616, 4, 64, 64), (17, 1032, 1160, 8, 64, 64), (520, 2056, 2056, 8, 128, 128),
+          (520, 2056, 2056, 4, 128, 128), (4000, 4040, 4072, 4, 512, 256), (744, 1032, 11072, 8, 64, 256),
+          (1232, 72, 5048, 4, 64, 256)]
 
 
-@pytest.mark.parametrize("N,m,n,d", SHAPES)
-def test_products_on_every_tile(lc, N, m, n, d):
+@pytest.mark.parametrize("N,m,n,d,tile_fwd,tile_dx", SHAPES)
+def test_products_on_every_tile(lc, N, m, n, d, tile_fwd, tile_dx):
     import torch
+    assert (product_tile("fwd", N, m, n), product_tile("dx", N, m, n)) == (tile_fwd, tile_dx)
     print(f"\ntiles N={N} m={m} n={n} d={d}", flush=True)
     inp = synth.layer_inputs(N, m, n, d, "bf16", k=N + m + n + d, z_lo=-1.0, z_hi=4.0)
     Z, X, dY = (to_dev(inp[k], "bf16") for k in ("Z", "X", "dY"))
