@@ -70,3 +70,22 @@ def test_packed_rows_four_waves(lc, N, m, n, d):
     ref = orc.linear_forward_packed(P[rows], A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
     assert_close(to_host(got[0])[:, rows], ref, 2e-2, "Y")
     assert all(torch.equal(got[0].view(torch.int32), g.view(torch.int32)) for g in got[1:])
+
+
+@pytest.mark.parametrize("N", [5, 16])
+@pytest.mark.parametrize("m,n,d", [(136, 4096, 8), (200, 16576, 4), (136, 28736, 8), (72, 33088, 4)])
+def test_parts_of_s(lc, N, m, n, d):
+    """s from 16 parts of one step to 29 of four, with an offset that dominates the output,
+    so that a part left out or taken twice is far beyond the tolerance."""
+    import torch
+    print(f"\npacked parts of s N={N} m={m} n={n} d={d}", flush=True)
+    r = synth.rng(N + m + n + d)
+    P = r.integers(0, 256, size=(m, n // 4), dtype=np.uint8)
+    Xb = synth.draw_activations(N, n, 7 + N, "bf16")
+    A, b = synth.draw_map(d, 1)
+    b = (100.0 * b).astype(np.float32)
+    Y = lc.linear_fwd_packed(torch.from_numpy(P).cuda(), torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda(),
+                             to_dev(Xb, "bf16"), d)
+    torch.cuda.synchronize()
+    ref = orc.linear_forward_packed(P, A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
+    assert_close(to_host(Y), ref, 2e-2, "Y")
