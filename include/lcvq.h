@@ -241,9 +241,10 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
  * lcvq_linear_fwd_packed_noalloc -- lcvq_linear_fwd_packed for callers that
  * cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid allocation): the same kernels and the same
- * results bit for bit, with the workspace replaced by a fixed array of
- * lcvq_packed_scratch_bytes() = 8 MiB that the library holds per device until
- * the process ends.  Nothing is allocated by this call.  The caller still
+ * results bit for bit (more than 16 tokens of n above 65280, of which 64 do not
+ * fit in the array, may differ in the last bits), with the workspace replaced by a
+ * fixed array of lcvq_packed_scratch_bytes() = 8 MiB that the library holds per
+ * device until the process ends.  Nothing is allocated by this call.  The caller still
  * passes inputs and outputs; every other argument is as in
  * lcvq_linear_fwd_packed.
  *   - A shape whose workspace (lcvq_workspace_bytes(LCVQ_OP_FWD_PACKED, ...))

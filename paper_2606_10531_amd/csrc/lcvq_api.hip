@@ -267,7 +267,7 @@ size_t lcvq_workspace_bytes(int32_t op, int64_t N, int64_t m, int64_t n, int32_t
   if (op == LCVQ_OP_BWD) return bwd_layout(N, m, n, bf16).total;
   if (op == LCVQ_OP_FWD_PACKED) {
     if (!bf16) return 0;
-    return up256((size_t)std::max(lcvq::packed_narrow(n).bytes, lcvq::packed_wide_bytes(N, n)));
+    return up256((size_t)std::max({lcvq::packed_narrow(n).bytes, lcvq::packed_split_bytes(n), lcvq::packed_wide_bytes(N, n)}));
   }
   return 0;
 }
@@ -537,24 +537,27 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
     }
     return ok();
   }
+  lcvq::PackedSplit split = lcvq::packed_split(m, n);
+  if (workspace_bytes < (size_t)split.bytes) split = lcvq::PackedSplit{};  // not split
   for (int64_t t0 = 0; t0 < N; t0 += 16) {
     const int Nc = (int)std::min<int64_t>(16, N - t0);
     const uint16_t *Xc = (const uint16_t *)X + t0 * n;
     char *Yc = (char *)Y + t0 * m * ys;
     if (lcvq::packed_fused(Nc)) {  // the product transforms X itself
       Timed tm(LCVQ_K_PACKED, st);
-      e = tm.done(lcvq::launch_packed_fused(narrow, packed, m, n, Xc, Nc, d, A, b, Yc, y_dtype == LCVQ_BF16, st));
+      e = tm.done(lcvq::launch_packed_fused(narrow, split, packed, m, n, ws, Xc, Nc, d, A, b, Yc, y_dtype == LCVQ_BF16, st));
       if (e != hipSuccess) return hip_fail(e, "packed product launch");
       continue;
     }
     {
       Timed tm(LCVQ_K_PACKED_PREP, st);
-      e = tm.done(lcvq::launch_packed_xprep(Xc, Nc, n, narrow.KT, narrow.spp, narrow.parts, d, A, b, (uint16_t *)ws,
-                                            (float *)(ws + narrow.sp), 16, st));
+      e = tm.done(lcvq::launch_packed_xprep(Xc, Nc, n, narrow.KT, split.spans ? split.spp : narrow.spp,
+                                            split.spans ? split.parts : narrow.parts, d, A, b, (uint16_t *)ws,
+                                            (float *)(ws + (split.spans ? split.sp : narrow.sp)), 16, st));
       if (e != hipSuccess) return hip_fail(e, "packed prepass launch");
     }
     Timed tm(LCVQ_K_PACKED, st);
-    e = tm.done(lcvq::launch_packed(narrow, packed, m, n, ws, Nc, Yc, y_dtype == LCVQ_BF16, st));
+    e = tm.done(lcvq::launch_packed(narrow, split, packed, m, n, ws, Nc, Yc, y_dtype == LCVQ_BF16, st));
     if (e != hipSuccess) return hip_fail(e, "packed product launch");
   }
   return ok();
@@ -568,7 +571,7 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
 // only a stand-in for the symbol, so its device address is looked up once per
 // device (hipGetSymbolAddress, with that device current) and only that address
 // is ever passed to kernels.
-static constexpr size_t kScratchBytes = (size_t)8 << 20;
+static constexpr size_t kScratchBytes = (size_t)lcvq::kPackedScratchBytes;
 static __device__ __align__(256) char scratch[kScratchBytes];
 
 namespace {

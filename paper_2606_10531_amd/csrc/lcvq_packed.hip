@@ -11,9 +11,10 @@
 // lcvq_packed_wide.hip.
 //
 // Block: 16 MR weight rows; its kW waves split K (256-wide steps w, w + kW, ...) and
-// add their tiles in LDS at the end, in wave order.  No split over blocks, so no
-// second launch, counters or partial tiles in memory: small matrices get their
-// parallelism from short tiles and many waves.  Each wave has two stages: the loads of
+// add their tiles in LDS at the end, in wave order.  K is not split over blocks, so there
+// is no second launch and no partial tile in memory (small matrices get their
+// parallelism from short tiles and many waves), except for few rows over more than 32512
+// columns (packed_split).  Each wave has two stages: the loads of
 // its next step, X first, are issued before the current step is multiplied, and that
 // starts with X and takes two row blocks of codes at a time as they arrive, so that
 // little is left to do behind the last load.
@@ -53,12 +54,16 @@ __device__ __forceinline__ void static_for(F f) {
 constexpr int kNarrowParts = 32;  // most parts of s of a pass
 
 // kD: group size when the block transforms X itself, for up to kTok = 2 or 4 tokens;
-// 0 when X' and the parts of s are ready in xq and sp.
-template <int MR, int kW, int kD, int kTok>
+// 0 when X' and the parts of s are ready in xq and sp.  kSplit: block (x, y) takes the
+// steps [y span, (y + 1) span) and stores its sums in `part` (span y, token, row), the
+// first row tile also its part of s (fused) in `part_s` (span y, 16 tokens), for
+// k_packed_sum.
+template <int MR, int kW, int kD, int kTok, bool kSplit = false>
 __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
     const uint8_t *__restrict__ packed, int64_t m, int64_t n, int KT, const uint16_t *__restrict__ xq,
     const float *__restrict__ sp, int parts, const uint16_t *__restrict__ X, const float *__restrict__ A,
-    const float *__restrict__ b, int Nc, void *__restrict__ Y, int y_bf16) {
+    const float *__restrict__ b, int Nc, void *__restrict__ Y, int y_bf16, int span, float *__restrict__ part,
+    float *__restrict__ part_s) {
   constexpr bool kFused = kD > 0;
   constexpr int kD1 = kFused ? kD : 8;
   constexpr int kH = 4 / kTok;                  // lanes that share a run of 16 columns
@@ -69,6 +74,8 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
   const int tid = threadIdx.x, lane = tid & 63, q = lane >> 4, c16 = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t r0 = (int64_t)blockIdx.x * 16 * MR, ldb = n / 4;
+  const int j0 = kSplit ? (int)blockIdx.y * span : 0;
+  if constexpr (kSplit) KT = min(KT, j0 + span);  // the block's steps
   const __amdgpu_buffer_rsrc_t rsA = make_rsrc(packed + r0 * ldb, (m - r0 < 16 * MR ? m - r0 : 16 * MR) * ldb);
   const __amdgpu_buffer_rsrc_t rsX = kFused ? make_rsrc(X, (int64_t)Nc * n * 2) : make_rsrc(xq, (int64_t)KT * 8192);
 
@@ -181,7 +188,7 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
     load_a(u, j);
     __builtin_amdgcn_sched_barrier(0);
   };
-  load(0, wave);
+  load(0, j0 + wave);
   if constexpr (kFused) {  // (behind the first loads: nothing waits for it before they are out)
 #pragma unroll
     for (int i = 0; i < kD1; ++i) {
@@ -193,7 +200,7 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
   // Steps in pairs, the last of an odd number behind the loop.  There is no way out
   // between the loads and the step they belong to: with one, the compiler had moved the
   // loads behind it, or waited for all of them at the loop's head.
-  int j = wave;
+  int j = j0 + wave;
   for (; j + kW < KT; j += 2 * kW) {
     load(1, j + kW);
     step(std::integral_constant<int, MR + kXL>{}, 0);
@@ -209,7 +216,7 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
     if constexpr (kH == 2) s += __shfl_xor(s, 16, 64);
   }
   float st = 0.0f;
-  if constexpr (!kFused) {  // read here, under the waits: behind the sums it costs up to 1 us
+  if constexpr (!kFused && !kSplit) {  // read here, under the waits: behind the sums it costs up to 1 us
     // the four lanes of a token take every fourth part (one lane for all of them was a
     // chain of loads: 14336 x 4096 at 16 tokens 11.1 us a call, now 9.9)
     if (wave < MR) {
@@ -233,6 +240,7 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
   if constexpr (kFused) {
 #pragma unroll
     for (int w = 0; w < kW; ++w) st += s_red[w * 4 + (c16 & 3)];
+    if (kSplit && blockIdx.x == 0 && tid < Nc) part_s[blockIdx.y * 16 + tid] = st;  // (lane t: token t)
   }
   // thread (rb, lane): rows 16 rb + 4 q + (0..3), token L % 16
   for (int rb = wave; rb < MR; rb += kW) {
@@ -241,6 +249,10 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
     floatx4 v = red[rb * 64 + lane];
 #pragma unroll
     for (int w = 1; w < kW; ++w) v += red[(w * MR + rb) * 64 + lane];
+    if constexpr (kSplit) {
+      *reinterpret_cast<floatx4 *>(part + ((int64_t)blockIdx.y * Nc + c16) * m + row) = v;
+      continue;
+    }
     const int64_t o = (int64_t)c16 * m + row;
     if (y_bf16) {
       uint2 w;
@@ -250,6 +262,31 @@ __global__ __launch_bounds__(64 * kW, kW == 16 || MR > 4 ? 1 : 2) void k_packed(
     } else {
       *reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(Y) + o) = v + st;
     }
+  }
+}
+
+// Four rows of a token per thread: the spans' sums in order, and s.
+__global__ __launch_bounds__(256) void k_packed_sum(const float *__restrict__ part, int spans, int64_t m, int Nc,
+                                                    const float *__restrict__ sp, int parts, void *__restrict__ Y,
+                                                    int y_bf16) {
+  const int64_t row = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  const int t = blockIdx.y, lane = threadIdx.x & 63;
+  float st = lane < parts ? sp[lane * 16 + t] : 0.0f;  // at most 64 parts, one per lane
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) st += __shfl_xor(st, o, 64);
+  if (row >= m) return;
+  const float *p = part + t * m + row;
+  floatx4 v = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+  for (int i = 0; i < spans; ++i) v += *reinterpret_cast<const floatx4 *>(p + (int64_t)i * Nc * m);
+  const int64_t o = (int64_t)t * m + row;
+  if (y_bf16) {
+    uint2 w;
+    w.x = pack_bf16x2(v[0] + st, v[1] + st);
+    w.y = pack_bf16x2(v[2] + st, v[3] + st);
+    *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Y) + o) = w;
+  } else {
+    *reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(Y) + o) = v + st;
   }
 }
 
@@ -274,9 +311,19 @@ bool packed_fused(int Nc) { return Nc <= 4; }
 // 4096 x 4096 10.7 -> 4.1; 16 tokens 25.7 -> 22.4, 32.7 -> 28.7, 15.4 -> 13.6, 20.2 -> 11.4 and
 // 12.5 -> 9.4.
 template <int kD, int kTok>
-static hipError_t launch(const uint8_t *packed, int64_t m, int64_t n, const PackedNarrow &p, const uint16_t *xq,
-                         const float *sp, const uint16_t *X, const float *A, const float *b, int Nc, void *Y, bool y_bf16,
+static hipError_t launch(const uint8_t *packed, int64_t m, int64_t n, const PackedNarrow &p, const PackedSplit &split,
+                         char *ws, const uint16_t *X, const float *A, const float *b, int Nc, void *Y, bool y_bf16,
                          hipStream_t st) {
+  const uint16_t *xq = kD > 0 ? nullptr : (const uint16_t *)ws;
+  const float *sp = kD > 0 ? nullptr : (const float *)(ws + p.sp);
+  if (split.spans > 0) {
+    float *part_s = (float *)(ws + split.sp), *part = (float *)(ws + split.part);
+    k_packed<4, 4, kD, kTok, true><<<dim3((unsigned)ceil_div(m, 64), (unsigned)split.spans), 256, 0, st>>>(
+        packed, m, n, p.KT, xq, nullptr, 0, X, A, b, Nc, Y, 0, split.span, part, part_s);
+    k_packed_sum<<<dim3((unsigned)ceil_div(m, 1024), (unsigned)Nc), 256, 0, st>>>(
+        part, split.spans, m, Nc, part_s, kD > 0 ? split.spans : split.parts, Y, y_bf16 ? 1 : 0);
+    return hipGetLastError();
+  }
   const int64_t rb = ceil_div(m, 16), rounds = ceil_div(rb, 256 * 8);
   const int mr = (int)ceil_div(rb, 256 * rounds);
   using K = decltype(&k_packed<1, 8, kD, kTok>);
@@ -297,7 +344,8 @@ static hipError_t launch(const uint8_t *packed, int64_t m, int64_t n, const Pack
       waves = 4;
     }
   }
-  k<<<(unsigned)ceil_div(rb, mr), 64 * waves, 0, st>>>(packed, m, n, p.KT, xq, sp, p.parts, X, A, b, Nc, Y, y_bf16 ? 1 : 0);
+  k<<<(unsigned)ceil_div(rb, mr), 64 * waves, 0, st>>>(packed, m, n, p.KT, xq, sp, p.parts, X, A, b, Nc, Y, y_bf16 ? 1 : 0, 0,
+                                                        nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -314,16 +362,48 @@ PackedNarrow packed_narrow(int64_t n) {
   return p;
 }
 
-hipError_t launch_packed(const PackedNarrow &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc, void *Y,
-                         bool y_bf16, hipStream_t st) {
-  return launch<0, 4>(packed, m, n, p, (const uint16_t *)ws, (const float *)(ws + p.sp), nullptr, nullptr, nullptr, Nc, Y,
-                      y_bf16, st);
+// Blocks of 64 rows that split K where up to 6144 rows meet 128 steps of K or more: one
+// block's chain of steps is then longer than the second launch that adds the spans (a
+// block for each compute unit, or two above 4096 rows; at most 16 spans).  Us a call,
+// split / not, at 1, 4 and 16 tokens: 1024 x 65536 10.6 / 21.3, 14.3 / 30.7 and 18 / 42; 4096 x
+// 40960 15.1 / 15.1, 17.1 / 21.1 and 22 / 30; 5120 x 131008 44 / 55, 49 / 74 and 62 / 101.  Not
+// below: 2048 x 28672 9.9 / 11.1 and 11.7 / 15.4, but 18.4 / 17.9 at 16, 4096 x 28672 12.1 / 11.4;
+// nor with more rows: 8192 x 65536 37.8 / 33.9 at one token.  The workspace does not depend
+// on m, and what does not fit in the fixed array is not split with a workspace either, so
+// that both give the same bits.
+constexpr int64_t kMaxSplitRows = 32768;  // spans times rows
+int64_t packed_split_bytes(int64_t n) {
+  const PackedNarrow w = packed_narrow(n);
+  const int64_t bytes = round_up(w.bytes, 256) + 64 * 64 + kMaxSplitRows * 64;
+  return w.KT < 128 || bytes > kPackedScratchBytes ? 0 : bytes;
 }
 
-hipError_t launch_packed_fused(const PackedNarrow &p, const uint8_t *packed, int64_t m, int64_t n, const uint16_t *X, int Nc,
-                               int d, const float *A, const float *b, void *Y, bool y_bf16, hipStream_t st) {
+PackedSplit packed_split(int64_t m, int64_t n) {
+  PackedSplit p{};
+  const PackedNarrow w = packed_narrow(n);
+  const int64_t tiles = ceil_div(m, 64);
+  if (packed_split_bytes(n) == 0 || tiles < 1 || tiles > 96) return p;
+  const int64_t most = std::min<int64_t>((tiles > 64 ? 512 : 256) / tiles, 16);
+  p.span = (int)ceil_div(w.KT, most);
+  p.spans = (int)ceil_div(w.KT, p.span);
+  p.spp = std::max(4, (int)ceil_div(w.KT, 64));
+  p.parts = (int)ceil_div(w.KT, p.spp);
+  p.sp = round_up(w.bytes, 256);
+  p.part = p.sp + 64 * 64;  // at most 64 parts of s of 16 tokens
+  p.bytes = p.part + p.spans * m * 64;
+  return p;
+}
+
+hipError_t launch_packed(const PackedNarrow &p, const PackedSplit &split, const uint8_t *packed, int64_t m, int64_t n,
+                         char *ws, int Nc, void *Y, bool y_bf16, hipStream_t st) {
+  return launch<0, 4>(packed, m, n, p, split, ws, nullptr, nullptr, nullptr, Nc, Y, y_bf16, st);
+}
+
+hipError_t launch_packed_fused(const PackedNarrow &p, const PackedSplit &split, const uint8_t *packed, int64_t m,
+                               int64_t n, char *ws, const uint16_t *X, int Nc, int d, const float *A, const float *b,
+                               void *Y, bool y_bf16, hipStream_t st) {
   auto go = d == 8 ? (Nc <= 2 ? launch<8, 2> : launch<8, 4>) : (Nc <= 2 ? launch<4, 2> : launch<4, 4>);
-  return go(packed, m, n, p, nullptr, nullptr, X, A, b, Nc, Y, y_bf16, st);
+  return go(packed, m, n, p, split, ws, X, A, b, Nc, Y, y_bf16, st);
 }
 
 }  // namespace lcvq

@@ -94,10 +94,23 @@ bool packed_fused(int Nc);
 // X' in operand order and the parts of s (rows of Tp) for tokens 0 .. Nc - 1
 hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int spp, int parts, int d, const float *A,
                                const float *b, uint16_t *xq, float *sp, int Tp, hipStream_t st);
-hipError_t launch_packed(const PackedNarrow &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc, void *Y,
-                         bool y_bf16, hipStream_t st);
-hipError_t launch_packed_fused(const PackedNarrow &p, const uint8_t *packed, int64_t m, int64_t n, const uint16_t *X, int Nc,
-                               int d, const float *A, const float *b, void *Y, bool y_bf16, hipStream_t st);
+// K split over `spans` blocks of `span` steps where few rows meet a long K (spans 0: not
+// split).  It has parts of s of its own, `spp` steps each (or one per span where the
+// product transforms X), and takes, behind the narrow pass's workspace, rows of 16 of
+// them at byte sp and the spans' sums at byte part; `bytes` is the whole workspace, at most
+// packed_split_bytes(n), which lcvq_workspace_bytes asks for.
+constexpr int64_t kPackedScratchBytes = (int64_t)8 << 20;  // of lcvq_linear_fwd_packed_noalloc
+struct PackedSplit {
+  int spans, span, spp, parts;
+  int64_t sp, part, bytes;
+};
+PackedSplit packed_split(int64_t m, int64_t n);
+int64_t packed_split_bytes(int64_t n);
+hipError_t launch_packed(const PackedNarrow &p, const PackedSplit &split, const uint8_t *packed, int64_t m, int64_t n,
+                         char *ws, int Nc, void *Y, bool y_bf16, hipStream_t st);
+hipError_t launch_packed_fused(const PackedNarrow &p, const PackedSplit &split, const uint8_t *packed, int64_t m,
+                               int64_t n, char *ws, const uint16_t *X, int Nc, int d, const float *A, const float *b,
+                               void *Y, bool y_bf16, hipStream_t st);
 // The same for more than 16 tokens, T tokens per pass (lcvq_packed_wide.hip); T = 0:
 // not used (few tokens, or `bytes` of workspace do not hold 64 tokens' X').  The
 // workspace holds X' of a pass and, at byte sp, `parts` rows of T partial sums of s.

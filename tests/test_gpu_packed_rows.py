@@ -1,6 +1,6 @@
 """The packed-codes forward up to 16 tokens on each of its blocks (16 to 128 rows, 4, 8
 and 16 waves, one and two rounds of blocks), with X transformed in the block (up to 2, up to 4 tokens) and by the
-prepass (5 and more), at ragged rows and K not a multiple of a step, with fewer steps
+prepass (5 and more), K whole or split over blocks, at ragged rows and K not a multiple of a step, with fewer steps
 than waves and with several per wave, against the oracle at 2e-2; a repeated call
 gives the same bits."""
 import numpy as np
@@ -89,3 +89,38 @@ def test_parts_of_s(lc, N, m, n, d):
     torch.cuda.synchronize()
     ref = orc.linear_forward_packed(P, A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
     assert_close(to_host(Y), ref, 2e-2, "Y")
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 16, 19])
+@pytest.mark.parametrize("m,n,d", [(8, 32768, 8), (200, 33088, 4), (1032, 40960, 8), (4104, 32832, 8), (6136, 34048, 4)])
+def test_long_rows(lc, N, m, n, d):
+    """Few rows over 128 steps of K and more, K split over blocks (up to 16 spans, the last
+    one short), on sampled rows: with a workspace of NaN, in the fixed array (the same
+    bits), and unsplit in a workspace that has no room for the spans' sums."""
+    import torch
+    print(f"\npacked long rows N={N} m={m} n={n} d={d}", flush=True)
+    r = synth.rng(N + m + n + d)
+    P = r.integers(0, 256, size=(m, n // 4), dtype=np.uint8)
+    Xb = synth.draw_activations(N, n, 7 + N, "bf16")
+    A, b = synth.draw_map(d, 1)
+    b = (100.0 * b).astype(np.float32)
+    Pd, X = torch.from_numpy(P).cuda(), to_dev(Xb, "bf16")
+    Ad, bd = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    need = lc.workspace_bytes(lc.OP_FWD_PACKED, N, m, n, d, torch.bfloat16)
+    Y = [torch.full((N, m), float("nan"), dtype=torch.float32, device="cuda") for _ in range(4)]
+    for y in Y[:2]:
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+        lc.linear_fwd_packed(Pd, Ad, bd, X, d, workspace=ws, out=y)
+    lc.linear_fwd_packed_noalloc(Pd, Ad, bd, X, d, out=Y[2])
+    small = torch.empty(-(-n // 256) * 8192 + 32 * 64, dtype=torch.uint8, device="cuda")   # X' and the parts of s
+    st = lc._lib.load().lcvq_linear_fwd_packed(N, m, n, d, Pd.data_ptr(), Ad.data_ptr(), bd.data_ptr(), X.data_ptr(),
+                                               Y[3].data_ptr(), lc._lib.F32, small.data_ptr(), small.numel(),
+                                               torch.cuda.current_stream().cuda_stream)
+    assert st == lc._lib.OK
+    torch.cuda.synchronize()
+    assert all(torch.equal(Y[0].view(torch.int32), y.view(torch.int32)) for y in Y[1:3])
+    rows = np.unique(np.concatenate([np.arange(min(m, 136)), np.arange(m // 2, m // 2 + 64) % m,
+                                     np.arange(max(m - 136, 0), m)]))
+    ref = orc.linear_forward_packed(P[rows], A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
+    assert_close(to_host(Y[0])[:, rows], ref, 2e-2, "Y")
+    assert_close(to_host(Y[3])[:, rows], ref, 2e-2, "Y unsplit")

@@ -27,3 +27,15 @@ def test_packed_passes_fit_one_grid():
     one = lc.workspace_bytes(lc.OP_FWD_PACKED, 64, m, n, 8, torch.bfloat16) / 64
     tokens = lc.workspace_bytes(lc.OP_FWD_PACKED, 1 << 20, m, n, 8, torch.bfloat16) / one
     assert tokens * m / 16 < 2 ** 32
+
+
+def test_packed_long_rows_have_room_for_spans():
+    """From 128 steps of 256 columns on, few rows split K over blocks: up to 32768 spans times
+    rows of 16 fp32 sums.  The size does not depend on the out-features, and the split is
+    left out where the 8 MiB of the call without a workspace do not hold it."""
+    size = lambda m, n: lc.workspace_bytes(lc.OP_FWD_PACKED, 16, m, n, 8, torch.bfloat16)  # noqa: E731
+    for n in (32768, 65536, 131072):
+        assert size(64, n) >= n // 256 * 8192 + 32768 * 64
+        assert size(64, n) == size(4096, n) == size(28672, n) <= 8 << 20
+    assert size(64, 28672) < 112 * 8192 + 8192
+    assert size(64, 262144 - 256) < (8 << 20)
