@@ -219,9 +219,10 @@ lcvq_status_t lcvq_linear_fwd_ex(int64_t N, int64_t m, int64_t n, int32_t d, int
  * App. A.2 without ever forming W_hat).  Up to 16 tokens are one pass over the
  * packed codes (m * n / 4 bytes, the only large operand); more are taken in as few
  * passes as the workspace allows (2 n bytes per token, whole 64-token tiles), with
- * the same bits whatever the number of passes, or 16 at a time when it holds fewer
- * than 64 tokens (sums in another order: the last bits may differ from those of
- * wide passes).
+ * the same bits whatever the number of passes, or 16 at a time (sums in another
+ * order: the last bits may differ from those of wide passes) when it holds fewer
+ * than 64 tokens and, whatever it holds, where that is faster (up to some 48 tokens
+ * of few out-features and many in-features; the sizes alone decide).
  *   N, m, n    tokens, out-features, in-features; d in {4, 8}
  *   packed     m * n / 4 bytes of codes (device, 16-byte aligned)
  *   A, b       map and offset, fp32 (device)

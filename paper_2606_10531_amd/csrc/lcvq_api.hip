@@ -522,7 +522,7 @@ lcvq_status_t lcvq_linear_fwd_packed(int64_t N, int64_t m, int64_t n, int32_t d,
   char *ws = (char *)workspace;
   const lcvq::PackedWidePlan wide =
       lcvq::packed_wide_plan(N, n, (int64_t)std::min<size_t>(workspace_bytes, (size_t)lcvq::kPackedWideBytes));
-  if (wide.T > 0) {
+  if (wide.T > 0 && !lcvq::packed_passes(N, m, n)) {
     for (int64_t t0 = 0; t0 < N; t0 += wide.T) {
       const int Nc = (int)std::min<int64_t>(wide.T, N - t0);
       {

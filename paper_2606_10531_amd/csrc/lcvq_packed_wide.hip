@@ -265,8 +265,8 @@ constexpr int64_t kMaxPassTokens = (int64_t)1 << 15;
 // Tokens per pass: as many whole 64-token tiles as `bytes` hold, in passes of equal
 // size.  A token's result does not depend on the pass or the tile it falls in (the
 // waves' shares of K, the order of their sums and the parts of s follow from n alone),
-// so every workspace of at least 64 tokens gives the same bits; 16-token passes sum in
-// another order.
+// so every workspace of at least 64 tokens gives the same bits; 16-token passes, which
+// packed_passes picks by the sizes alone, sum in another order.
 PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes) {
   PackedWidePlan p{};
   p.KT = (int)ceil_div(n, kWk);
@@ -297,12 +297,31 @@ hipError_t launch_packed_xprep(const uint16_t *X, int Nc, int64_t n, int KT, int
   return hipGetLastError();
 }
 
+// ns per 64 K of the tiles of a pass, 128 or 64 rows (one tile with the chip full, times the
+// rounds of tiles over the compute units)
+static int64_t wide_ns(int64_t N, int64_t m, bool four) {
+  return (four ? 187 : 117) * ceil_div(ceil_div(m, four ? 128 : 64) * ceil_div(N, 64), 256);
+}
+
+// Whether passes of 16 tokens finish sooner: a wide tile's four waves take KT / 4 steps each
+// whatever the tokens, so with few tokens and few rows over a long K they leave the chip
+// idle.  ns, fitted to 648 calls of 17 .. 48 tokens, 64 .. 28672 rows and 1024 .. 40960 columns
+// (the pick is 0.3 % from the faster one on average, 15 % at most).  Measured, us, wide /
+// passes: 17 tokens of 1088 x 24000 46.8 / 24.6, 2048 x 28672 51.8 / 26.7, 4096 x 11008 24.3 /
+// 16.5; 32 tokens of 1024 x 28672 52.7 / 32, 8192 x 28672 51.0 / 40.3; but 48 of 8192 x 28672 51.7 /
+// 60, 32 of 4096 x 4096 13.2 / 15.3 and 17 of 28672 x 8192 30.6 / 33.3.
+bool packed_passes(int64_t N, int64_t m, int64_t n) {
+  const int64_t KT = ceil_div(n, kWk), rest = N % 16;
+  const int64_t wide = 6500 + KT * std::min(wide_ns(N, m, true), wide_ns(N, m, false)) * 7 / 2;
+  const int64_t pass = 5500 + 80 * KT + m * n / 32000;
+  // the last pass transforms X itself, if it is of up to four tokens
+  return N / 16 * pass + (rest == 0 ? 0 : rest <= 2 ? pass * 7 / 10 : rest <= 4 ? pass * 17 / 20 : pass) < wide;
+}
+
 hipError_t launch_packed_wide(const PackedWidePlan &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc,
                               void *Y, bool y_bf16, hipStream_t st) {
-  // 128 or 64 rows per tile: rounds of tiles over the compute units times a tile's
-  // time per 64 K (ns, measured with the chip full)
-  const int64_t tt = ceil_div(Nc, 64), t4 = ceil_div(m, 128) * tt, t2 = ceil_div(m, 64) * tt;
-  const bool four = 187 * ceil_div(t4, 256) <= 117 * ceil_div(t2, 256);
+  const int64_t tt = ceil_div(Nc, 64);
+  const bool four = wide_ns(Nc, m, true) <= wide_ns(Nc, m, false);
   const int tiles_m = (int)ceil_div(m, four ? 128 : 64);
   auto k = four ? (y_bf16 ? k_packed_wide<4, true> : k_packed_wide<4, false>)
                 : (y_bf16 ? k_packed_wide<2, true> : k_packed_wide<2, false>);

@@ -123,6 +123,7 @@ struct PackedWidePlan {
 };
 PackedWidePlan packed_wide_plan(int64_t N, int64_t n, int64_t bytes);
 int64_t packed_wide_bytes(int64_t N, int64_t n);
+bool packed_passes(int64_t N, int64_t m, int64_t n);  // 16 tokens at a time are faster
 hipError_t launch_packed_wide(const PackedWidePlan &p, const uint8_t *packed, int64_t m, int64_t n, const char *ws, int Nc,
                               void *Y, bool y_bf16, hipStream_t st);
 

@@ -69,3 +69,29 @@ def test_packed_wide_with_a_workspace_for_few_tokens(lc):
     torch.cuda.synchronize()
     ref = orc.linear_forward_packed(P, A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
     assert_close(to_host(Y), ref, TOL, "Y")
+
+
+@pytest.mark.parametrize("N,m,n,d,passes", [(17, 1088, 24000, 4, True), (32, 2048, 28672, 8, True), (20, 8192, 11008, 8, True),
+                                            (33, 72, 40960, 4, True), (48, 8192, 28672, 8, False), (17, 264, 1088, 8, False),
+                                            (65, 1088, 24000, 8, False)])
+def test_few_tokens_and_rows_over_long_k(lc, N, m, n, d, passes):
+    """Where wide tiles would leave the chip idle, more than 16 tokens go 16 at a time: the same
+    bits as calls of up to 16 tokens; elsewhere the wide tiles' own."""
+    import torch
+    print(f"\npacked passes N={N} m={m} n={n} d={d}", flush=True)
+    r = synth.rng(N + m + n + d)
+    P = r.integers(0, 256, size=(m, n // 4), dtype=np.uint8)
+    Xb = synth.draw_activations(N, n, 7 + N, "bf16")
+    A, b = synth.draw_map(d, 1)
+    Pd, X = torch.from_numpy(P).cuda(), to_dev(Xb, "bf16")
+    Ad, bd = torch.from_numpy(A).cuda(), torch.from_numpy(b).cuda()
+    Y = lc.linear_fwd_packed(Pd, Ad, bd, X, d, out_dtype=torch.float32)
+    Y2 = torch.full((N, m), float("nan"), dtype=torch.float32, device="cuda")
+    lc.linear_fwd_packed_noalloc(Pd, Ad, bd, X, d, out=Y2)
+    parts = torch.cat([lc.linear_fwd_packed(Pd, Ad, bd, X[i:i + 16], d, out_dtype=torch.float32) for i in range(0, N, 16)])
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(torch.int32), Y2.view(torch.int32))
+    assert torch.equal(Y.view(torch.int32), parts.view(torch.int32)) == passes
+    rows = np.unique(np.concatenate([np.arange(min(m, 136)), np.arange(max(m - 136, 0), m)]))
+    ref = orc.linear_forward_packed(P[rows], A.astype(np.float64), b.astype(np.float64), orc.widen(Xb, "bf16"), d, n)
+    assert_close(to_host(Y)[:, rows], ref, TOL, "Y")
