@@ -1014,13 +1014,18 @@ hipError_t launch_map_combine(const float *mapp, int rows, int d, int accumulate
 }
 
 // Which weight-gradient tile: the time of the busiest compute unit, ns per 64-token step
-// and per block, plus a part per block for the chip filling up, fitted to 107 shapes of
-// 64 .. 16384 tokens and 512 .. 28672 features (which it gives to 4 .. 9 %): 256 x 256, one
-// block per unit; 256 x 128, two blocks side by side or one alone; 128 x 64 with the
-// tokens split over the waves (steps of 256 tokens), two or one.  Measured (us, full /
-// half / split): 4096^3 100 / 106 / 137; 512 tokens of 28672 x 8192 332 / 290 / 466 (the
-// epilogue counts); 4096 of 2048 x 2048 82 / 64 / 42 and 16384 of 1024 x 2048 295 / 230 / 76
-// (few tiles); 12130 of 16296 x 592 240 / 309 / 337; 5322 of 784 x 10408 111 / 128 / 129.
+// and per block, plus a part per block for the chip filling up: 256 x 256, one block per
+// unit; 256 x 128, two blocks side by side or one alone; 128 x 64 with the tokens split
+// over the waves (steps of 256 tokens), two or one.  Past about 200 MB the operands fall out
+// of the 256 MB last-level cache, and the smaller tiles, which read them more often, take
+// longer than that (12000 tokens of 1040 x 20000, us, full / half / split: 516 / 559 / 781,
+// 16000 of 24120 x 520 620 / 621 / 716): they count 1.08 and 1.2 times.  The epilogue (dZ of 2
+// or 4 bytes, added or not, the estimator) is not a term.  Over 213 shapes of 64 .. 16384
+// tokens and 512 .. 28672 features and three epilogues each (bf16, fp32 added to, estimator)
+// the pick is 0.6 % from the fastest tile on average, 19 % at most (436 tokens of 3600 x 2152
+// into fp32, 29 against 25 us), and never 0.5 % slower than 256 x 256.  Measured: 4096^3 100 / 106 / 137; 512
+// tokens of 28672 x 8192 332 / 290 / 466; 4096 of 2048 x 2048 82 / 64 / 42 and 16384 of 1024 x
+// 2048 295 / 230 / 76 (few tiles).
 enum DwTile { kDwFull, kDwHalf, kDwSplit };
 static DwTile dw_tile(int64_t m, int64_t n, int64_t KBt) {
   struct Cost {  // ns: two blocks (per step, each), one block, per 256 blocks, in all
@@ -1032,9 +1037,11 @@ static DwTile dw_tile(int64_t m, int64_t n, int64_t KBt) {
            blocks * (c.full_step * steps + c.full) / 256 + c.base;
   };
   const int64_t cols = ceil_div(n, 256);
+  // operands (2 bytes, each side's features by the tokens) beyond what the caches hold
+  const int64_t far = KBt * 64 * 2 * (m + n) > 200000000 ? 1 : 0;
   const int64_t full = cost({2100, 15200, 1050, 7600, 310, 2500, 3200}, cols * ceil_div(m, 256), KBt),
-                half = cost({1130, 4300, 810, 3800, 210, 1100, 2600}, cols * ceil_div(m, 128), KBt),
-                split = cost({1030, 2800, 670, 1800, 580, 300, 4600}, ceil_div(n, 128) * ceil_div(m, 64), KBt / 4);
+                half = cost({1130, 4300, 810, 3800, 210, 1100, 2600}, cols * ceil_div(m, 128), KBt) * (25 + 2 * far) / 25,
+                split = cost({1030, 2800, 670, 1800, 580, 300, 4600}, ceil_div(n, 128) * ceil_div(m, 64), KBt / 4) * (5 + far) / 5;
   return full <= half && full <= split ? kDwFull : half <= split ? kDwHalf : kDwSplit;
 }
 int dw_tile_rows(int64_t N, int64_t m, int64_t n) {
