@@ -346,15 +346,18 @@ __global__ __launch_bounds__(256, 2) void k_codes_split(
 // ---- the choice of tiles -----------------------------------------------------
 // A product's time by tile: per round of tiles over the 256 compute units a fixed part
 // (filling the pipeline, the epilogue) and a part per 64-wide step, plus a part per tile
-// and step (the chip filling up: power, operand traffic), fitted to both products of
-// 107 shapes of 64 .. 16384 tokens and 512 .. 28672 features, which it gives to 3 % for
-// the wide tile (512 x 128; input gradient 256 x 256) and 5 .. 10 % for the small ones.
-// Rows of dY that don't begin on 128-byte lines cost the small input-gradient tile,
-// which reads them in 128-byte runs, up to a fifth.  Measured (us, wide / 128 rows /
-// 64 rows): forward, 256 tokens of 4096 x 4096 80 / - / 12; 2048 of 4096 x 11008
-// 213 / 128 / -; 4228 of 23936 x 1128 196 / 228 / 292; 5262 of 6280 x 10136 596 / 471 /
-// 586.  Input gradient, 1000 of 11008 x 4096 217 / 79 / -; 958 of 26032 x 3176 483 / 169 /
-// 219; 2404 of 22736 x 10056 894 / 993 / 1473; 4096^3 108 / 129 / -.
+// and step (the chip filling up: power, operand traffic).  Rows of dY that don't begin on
+// 128-byte lines cost the small input-gradient tile, which reads them in 128-byte runs, up
+// to a fifth.  X' of more than 250 MB falls out of the last-level cache, and the small
+// tiles, which read it more often, count 1.15 times (us, wide / 128 rows / 64 rows: 16000
+// tokens of 776 x 16384 319 / 342 / 500, 12000 of 2064 x 20000 748 / 796 / 1134).  Over 214 shapes
+// of 64 .. 16384 tokens and 512 .. 28672 features the pick is 0.4 % from the fastest tile on
+// average for either product, and slower than the wide tile by more than 0.3 % only once
+// (1000 tokens of 1040 x 20000, input gradient, 75.8 against 74.0 us).  Measured: forward,
+// 256 tokens of 4096 x 4096 80 / - / 12; 2048 of 4096 x 11008 213 / 128 / -; 4228 of 23936 x
+// 1128 196 / 228 / 292; 5262 of 6280 x 10136 596 / 471 / 586.  Input gradient, 1000 of 11008 x
+// 4096 217 / 79 / -; 958 of 26032 x 3176 483 / 169 / 219; 2404 of 22736 x 10056 894 / 993 / 1473;
+// 4096^3 108 / 129 / -.
 int codes_split_slabs(int64_t rows, int64_t tokens, int64_t K, bool dx) {
   struct Cost {  // ns: per round and step, per round, per 256 tiles and step, in all
     int64_t step, round, full, base;
@@ -368,8 +371,10 @@ int codes_split_slabs(int64_t rows, int64_t tokens, int64_t K, bool dx) {
     return ceil_div(tiles, 256) * (c.step * KB + c.round) + tiles * full * KB / 256 + c.base;
   };
   const int64_t tt = ceil_div(tokens, 64);
+  const int64_t far = !dx && 2 * tokens * K > 250000000 ? 3 : 0;
   const int64_t c0 = cost(0, dx ? ceil_div(rows, 256) * ceil_div(tokens, 256) : ceil_div(rows, 512) * ceil_div(tokens, 128)),
-                c4 = cost(1, ceil_div(rows, 128) * tt), c2 = cost(2, ceil_div(rows, 64) * tt);
+                c4 = cost(1, ceil_div(rows, 128) * tt) * (20 + far) / 20,
+                c2 = cost(2, ceil_div(rows, 64) * tt) * (20 + far) / 20;
   if (c0 <= c4 && c0 <= c2) return 0;
   return c2 < c4 ? 2 : 4;
 }

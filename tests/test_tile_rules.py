@@ -12,3 +12,9 @@ from helpers import product_tile
                                         (1000, 11008, 4096, 128), (4096, 2048, 2048, 64), (16384, 1024, 2048, 64)])
 def test_weight_gradient(N, m, n, tile):
     assert product_tile("dw", N, m, n) == tile
+
+
+@pytest.mark.parametrize("N,m,n,tile", [(16000, 776, 16384, 512), (12000, 2064, 20000, 512), (4096, 4096, 4096, 512),
+                                        (2048, 4096, 11008, 128), (1000, 11008, 4096, 128), (256, 4096, 4096, 64)])
+def test_forward(N, m, n, tile):
+    assert product_tile("fwd", N, m, n) == tile
