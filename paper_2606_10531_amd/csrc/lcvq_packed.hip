@@ -307,9 +307,9 @@ bool packed_fused(int Nc) { return Nc <= 4; }
 // 35.8, 8192 x 8192 with 32 rows 7.0 -> 7.6).  Eight elsewhere.
 // Against 64-row blocks of four waves with K split over blocks and a prepass except for
 // long rows (one graph of calls, weights from memory, us): one token through 28672 x 8192
-// 16.1 -> 15.7, 8192 x 28672 23.1 -> 16.8, 4096 x 11008 13.0 -> 6.6, 11008 x 4096 14.7 -> 6.0,
-// 4096 x 4096 10.7 -> 4.1; 16 tokens 25.7 -> 22.4, 32.7 -> 28.7, 15.4 -> 13.6, 20.2 -> 11.4 and
-// 12.5 -> 9.4.
+// 15.9 -> 14.6, 8192 x 28672 22.3 -> 15.7, 4096 x 11008 12.8 -> 6.4, 11008 x 4096 14.3 -> 5.8,
+// 4096 x 4096 10.9 -> 4.3; 16 tokens 23.6 -> 20.4, 28.9 -> 25.1, 14.6 -> 10.7, 18.7 -> 9.1 and
+// 12.7 -> 8.1.
 template <int kD, int kTok>
 static hipError_t launch(const uint8_t *packed, int64_t m, int64_t n, const PackedNarrow &p, const PackedSplit &split,
                          char *ws, const uint16_t *X, const float *A, const float *b, int Nc, void *Y, bool y_bf16,
@@ -365,8 +365,8 @@ PackedNarrow packed_narrow(int64_t n) {
 // Blocks of 64 rows that split K where up to 6144 rows meet 128 steps of K or more: one
 // block's chain of steps is then longer than the second launch that adds the spans (a
 // block for each compute unit, or two above 4096 rows; at most 16 spans).  Us a call,
-// split / not, at 1, 4 and 16 tokens: 1024 x 65536 10.6 / 21.3, 14.3 / 30.7 and 18 / 42; 4096 x
-// 40960 15.1 / 15.1, 17.1 / 21.1 and 22 / 30; 5120 x 131008 44 / 55, 49 / 74 and 62 / 101.  Not
+// split / not, at 1, 4 and 16 tokens: 1024 x 65536 9.7 / 21.3, 10.7 / 30.7 and 17.1 / 41.8; 4096 x
+// 40960 14.5 / 15.1, 16.7 / 21.1 and 21.0 / 29.7; 2048 x 131008 20 / 39, 24 / 59 and 33 / 84.  Not
 // below: 2048 x 28672 9.9 / 11.1 and 11.7 / 15.4, but 18.4 / 17.9 at 16, 4096 x 28672 12.1 / 11.4;
 // nor with more rows: 8192 x 65536 37.8 / 33.9 at one token.  The workspace does not depend
 // on m, and what does not fit in the fixed array is not split with a workspace either, so
