@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256, 2) void k_codes_split(
 // 128-byte lines cost the small input-gradient tile, which reads them in 128-byte runs, up
 // to a fifth.  X' of more than 250 MB falls out of the last-level cache, and the small
 // tiles, which read it more often, count 1.15 times (us, wide / 128 rows / 64 rows: 16000
-// tokens of 776 x 16384 319 / 342 / 500, 12000 of 2064 x 20000 748 / 796 / 1134).  Over 214 shapes
+// tokens of 776 x 16384 319 / 342 / 500, 12000 of 2064 x 20000 748 / 796 / 1134).  Over 213 shapes
 // of 64 .. 16384 tokens and 512 .. 28672 features the pick is 0.4 % from the fastest tile on
 // average for either product, and slower than the wide tile by more than 0.3 % only once
 // (1000 tokens of 1040 x 20000, input gradient, 75.8 against 74.0 us).  Measured: forward,
